@@ -47,7 +47,7 @@ constexpr int unr_depth(int u) { return u % 100; }
 constexpr bool unr_pipe(int u) { return (u / 100) % 2 == 1; }
 constexpr bool unr_low(int u) { return u >= 200; }
 
-template <int PREC, int IPT, int TJ, int WG, bool EPS0, int UNR, int WPE>
+template <int PREC, int IPT, int TJ, int WG, bool EPS0, int UNR, int WPE, bool PRIO>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE > 0 ? WPE : 1)))
 void force_kernel(ForceArgs a) {
     constexpr bool LOW = unr_low(UNR);
@@ -55,17 +55,17 @@ void force_kernel(ForceArgs a) {
     __shared__ float losh[LOW && PREC == 1 ? 7 * IPT * WG : 1];
     const int jb = blockIdx.y * a.jchunk;
     const int je = min(a.nj, jb + a.jchunk);
-    force_block<PREC, IPT, TJ, WG, EPS0, false, unr_depth(UNR), unr_pipe(UNR), 0, LOW>(
+    force_block<PREC, IPT, TJ, WG, EPS0, false, unr_depth(UNR), unr_pipe(UNR), 0, LOW, PRIO>(
         a, sh, blockIdx.x * (WG * IPT), a.ni, jb, je, a.eps2, blockIdx.y, losh);
 }
 
 // The force-only (KIND 1) and nearest-neighbour (KIND 2) evaluations.
-template <int PREC, int KIND, int IPT, int TJ, int WG, bool EPS0, int UNR>
+template <int PREC, int KIND, int IPT, int TJ, int WG, bool EPS0, int UNR, bool PRIO>
 __global__ __launch_bounds__(WG) void force_kernel_kind(ForceArgs a) {
     __shared__ float4 sh[2][TJ * Rec<PREC>::R];
     const int jb = blockIdx.y * a.jchunk;
     const int je = min(a.nj, jb + a.jchunk);
-    force_block<PREC, IPT, TJ, WG, EPS0, false, unr_depth(UNR), unr_pipe(UNR), KIND>(
+    force_block<PREC, IPT, TJ, WG, EPS0, false, unr_depth(UNR), unr_pipe(UNR), KIND, false, PRIO>(
         a, sh, blockIdx.x * (WG * IPT), a.ni, jb, je, a.eps2, blockIdx.y);
 }
 
@@ -110,7 +110,7 @@ void force_kernel_js(ForceArgs a) {
 // work-group takes the next item from a device counter until none is left.
 // Within a cluster every particle is both an i and a j (self excluded);
 // there are no cross-cluster terms.
-template <int PREC, int IPT, int TJ, int WG>
+template <int PREC, int IPT, int TJ, int WG, bool PRIO>
 __global__ __launch_bounds__(WG) void force_batched_kernel(ForceArgs a, BatchArgs b) {
     __shared__ float4 sh[2][TJ * Rec<PREC>::R];
     __shared__ int item_sh;
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(WG) void force_batched_kernel(ForceArgs a, BatchArg
         const int2 it = b.items[item];
         const int beg = b.cbeg[it.x], end = b.cend[it.x];
         const double e = b.eps[it.x];
-        force_block<PREC, IPT, TJ, WG, false>(a, sh, beg + it.y * (WG * IPT), end, beg, end,
+        force_block<PREC, IPT, TJ, WG, false, false, 4, false, 0, false, PRIO>(a, sh, beg + it.y * (WG * IPT), end, beg, end,
                                               (float)(e * e), 0);
     }
 }
@@ -265,9 +265,29 @@ hipError_t launch_batch_plan(const PlanArgs& p, hipStream_t st) {
 
 // ---- variant table -----------------------------------------------------------
 
+// Whether a launch puts more than one wave on each of the 1024 SIMDs.  Below
+// that a wave issues alone: it never loses the two-wave issue that the
+// raised priority of rsq_group keeps, only pays for it (force-only at N =
+// 2000, 992 waves of one tile each, 2% slower; 64 float32 clusters of at
+// most 1024 bodies, 400 waves, 6%).  Direct launches whose ranges hold more
+// than one tile gain all the same, from the four records in flight (N = 2100,
+// 578 waves: 28.7 to 26.9 us); N = 3000, 2256 waves: 35.8 to 30.4 us.  The
+// short tiles serve one-tile ranges only.
+constexpr bool two_waves(int64_t groups, int wg) { return groups * wg > 1024 * 64; }
+template <int TJ>
+static bool use_prio(int64_t groups, int wg, const ForceArgs& a) {
+    return TJ >= 64 && (two_waves(groups, wg) || a.jchunk > TJ);
+}
+
 template <int PREC, int IPT, int TJ, int WG, bool EPS0, int UNR, int WPE>
 static hipError_t launch_one(int nb, int S, const ForceArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL((force_kernel<PREC, IPT, TJ, WG, EPS0, UNR, WPE>), dim3(nb, S), dim3(WG), 0, st, a);
+    if constexpr (TJ < 64) {
+        hipLaunchKernelGGL((force_kernel<PREC, IPT, TJ, WG, EPS0, UNR, WPE, false>), dim3(nb, S), dim3(WG), 0, st, a);
+    } else if (IPT > 1 || use_prio<TJ>((int64_t)nb * S, WG, a)) {
+        hipLaunchKernelGGL((force_kernel<PREC, IPT, TJ, WG, EPS0, UNR, WPE, true>), dim3(nb, S), dim3(WG), 0, st, a);
+    } else {
+        hipLaunchKernelGGL((force_kernel<PREC, IPT, TJ, WG, EPS0, UNR, WPE, IPT != 1>), dim3(nb, S), dim3(WG), 0, st, a);
+    }
     return hipGetLastError();
 }
 
@@ -279,14 +299,21 @@ static hipError_t launch_one_js(int nb, int S, const ForceArgs& a, hipStream_t s
 
 template <int PREC, int KIND, int IPT, int TJ, int WG, bool EPS0, int UNR>
 static hipError_t launch_kind(int nb, int S, const ForceArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL((force_kernel_kind<PREC, KIND, IPT, TJ, WG, EPS0, UNR>), dim3(nb, S), dim3(WG), 0, st, a);
+    if (IPT > 1 || use_prio<TJ>((int64_t)nb * S, WG, a))
+        hipLaunchKernelGGL((force_kernel_kind<PREC, KIND, IPT, TJ, WG, EPS0, UNR, true>), dim3(nb, S), dim3(WG), 0, st, a);
+    else
+        hipLaunchKernelGGL((force_kernel_kind<PREC, KIND, IPT, TJ, WG, EPS0, UNR, IPT != 1>), dim3(nb, S), dim3(WG), 0,
+                           st, a);
     return hipGetLastError();
 }
 
 template <int PREC, int IPT, int TJ, int WG, bool EPS0>
 static hipError_t launch_batched_one(int grid, const ForceArgs& a, const BatchArgs& b, hipStream_t st) {
     if (EPS0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((force_batched_kernel<PREC, IPT, TJ, WG>), dim3(grid), dim3(WG), 0, st, a, b);
+    if (two_waves(grid, WG))
+        hipLaunchKernelGGL((force_batched_kernel<PREC, IPT, TJ, WG, true>), dim3(grid), dim3(WG), 0, st, a, b);
+    else
+        hipLaunchKernelGGL((force_batched_kernel<PREC, IPT, TJ, WG, false>), dim3(grid), dim3(WG), 0, st, a, b);
     return hipGetLastError();
 }
 

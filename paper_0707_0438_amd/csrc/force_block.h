@@ -59,8 +59,10 @@ __device__ __forceinline__ void two_sum_fold(float& hi, float& lo, float p) {
 // compensated sums live in LDS (losh, 7 * IPT * WG floats: each lane
 // touches its own words once per tile) and the j tiles are single-buffered
 // (sh[0] only), so no staging registers stay live through the tile loop.
+// PRIO: v_rsq in groups at raised priority (rsq_group), for launches with
+// more than one wave per SIMD.
 template <int PREC, int IPT, int TJ, int WG, bool EPS0, bool JS = false, int UNR = 4, bool PIPE = false,
-          int KIND = 0, bool LOW = false>
+          int KIND = 0, bool LOW = false, bool PRIO = true>
 __device__ __forceinline__ void force_block(const ForceArgs& a, float4 (*sh)[TJ * Rec<PREC>::R], int ibase,
                                             int iend, int jb, int je, float eps2, int split,
                                             float* __restrict__ losh = nullptr) {
@@ -157,59 +159,71 @@ __device__ __forceinline__ void force_block(const ForceArgs& a, float4 (*sh)[TJ 
     // the instruction that reads it
     float eps2v;
     asm volatile("v_mov_b32 %0, %1" : "=v"(eps2v) : "s"(eps2));
-    // MASK (a std::integral_constant): the self pair j == selfk[k] gets zero
-    // mass, so it contributes exactly nothing to any sum.
-    auto interact = [&](auto maskc, const float4& q0, const float4& q1, const float4& q2, int jidx) {
+    // JB consecutive j records (the first with index jidx) against the lane's
+    // i, all rsq of the group together.  MASK (a std::integral_constant): the
+    // self pair j == selfk[k] gets zero mass, so it contributes exactly
+    // nothing to any sum.
+    auto interact = [&](auto maskc, auto jbc, const float4* q0, const float4* q1, const float4* q2, int jidx) {
         constexpr bool MASK = decltype(maskc)::value;
+        constexpr int JB = decltype(jbc)::value;
+        float dx[JB * IPT], dy[JB * IPT], dz[JB * IPT], s[JB * IPT], rinv[JB * IPT];
 #pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            const float mj = (MASK && !EPS0 && jidx == selfk[k]) ? 0.f : q0.w;
-            float dx, dy, dz;
-            if (PREC == 1) {
-                dx = (q0.x - ix[k]) + (q2.x - lx[k]);
-                dy = (q0.y - iy[k]) + (q2.y - ly[k]);
-                dz = (q0.z - iz[k]) + (q2.z - lz[k]);
-            } else {
-                dx = q0.x - ix[k];
-                dy = q0.y - iy[k];
-                dz = q0.z - iz[k];
+        for (int u = 0; u < JB; ++u)
+#pragma unroll
+            for (int k = 0; k < IPT; ++k) {
+                const int e = u * IPT + k;
+                if (PREC == 1) {
+                    dx[e] = (q0[u].x - ix[k]) + (q2[u].x - lx[k]);
+                    dy[e] = (q0[u].y - iy[k]) + (q2[u].y - ly[k]);
+                    dz[e] = (q0[u].z - iz[k]) + (q2[u].z - lz[k]);
+                } else {
+                    dx[e] = q0[u].x - ix[k];
+                    dy[e] = q0[u].y - iy[k];
+                    dz[e] = q0[u].z - iz[k];
+                }
+                if (KIND == 2) {
+                    const float r2 = fmaf(dz[e], dz[e], fmaf(dy[e], dy[e], dx[e] * dx[e]));
+                    s[e] = r2 + eps2v;
+                    const bool better = (r2 < bnr[k]) & (jidx + u != selfk[k]);
+                    bnr[k] = better ? r2 : bnr[k];
+                    bnj[k] = better ? jidx + u : bnj[k];
+                } else {
+                    s[e] = fmaf(dz[e], dz[e], fmaf(dy[e], dy[e], fmaf(dx[e], dx[e], eps2v)));
+                }
             }
-            float s;
-            if (KIND == 2) {
-                const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                s = r2 + eps2v;
-                const bool better = (r2 < bnr[k]) & (jidx != selfk[k]);
-                bnr[k] = better ? r2 : bnr[k];
-                bnj[k] = better ? jidx : bnj[k];
-            } else {
-                s = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, eps2v)));
-            }
-            float rinv = __builtin_amdgcn_rsqf(s);
-            if (EPS0) rinv = s > 0.f ? rinv : 0.f;
-            if (KIND == 1) {
-                const float mr = mj * rinv;
-                const float mr3 = mr * (rinv * rinv);
-                acc[k][0] = fmaf(mr3, dx, acc[k][0]);
-                acc[k][1] = fmaf(mr3, dy, acc[k][1]);
-                acc[k][2] = fmaf(mr3, dz, acc[k][2]);
-                acc[k][6] += mr;
-                continue;
-            }
-            const float ux = q1.x - iu[k], uy = q1.y - iv[k], uz = q1.z - iw[k];
-            const float rv = fmaf(dz, uz, fmaf(dy, uy, dx * ux));
-            const float rinv2 = rinv * rinv;
-            const float mr = mj * rinv;
-            const float mr3 = mr * rinv2;
-            const float al = 3.0f * rv * rinv2;
-            acc[k][0] = fmaf(mr3, dx, acc[k][0]);
-            acc[k][1] = fmaf(mr3, dy, acc[k][1]);
-            acc[k][2] = fmaf(mr3, dz, acc[k][2]);
-            acc[k][3] = fmaf(mr3, fmaf(-al, dx, ux), acc[k][3]);
-            acc[k][4] = fmaf(mr3, fmaf(-al, dy, uy), acc[k][4]);
-            acc[k][5] = fmaf(mr3, fmaf(-al, dz, uz), acc[k][5]);
-            acc[k][6] += mr;
+        if constexpr (PRIO) {
+            rsq_group(rinv, s);
+        } else {
+#pragma unroll
+            for (int e = 0; e < JB * IPT; ++e) rinv[e] = __builtin_amdgcn_rsqf(s[e]);
         }
+#pragma unroll
+        for (int u = 0; u < JB; ++u)
+#pragma unroll
+            for (int k = 0; k < IPT; ++k) {
+                const int e = u * IPT + k;
+                const float mj = (MASK && !EPS0 && jidx + u == selfk[k]) ? 0.f : q0[u].w;
+                const float ri = EPS0 && !(s[e] > 0.f) ? 0.f : rinv[e];
+                const float rinv2 = ri * ri;
+                const float mr = mj * ri;
+                const float mr3 = mr * rinv2;
+                acc[k][0] = fmaf(mr3, dx[e], acc[k][0]);
+                acc[k][1] = fmaf(mr3, dy[e], acc[k][1]);
+                acc[k][2] = fmaf(mr3, dz[e], acc[k][2]);
+                acc[k][6] = fmaf(mj, ri, acc[k][6]);
+                if (KIND == 1) continue;
+                const float ux = q1[u].x - iu[k], uy = q1[u].y - iv[k], uz = q1[u].z - iw[k];
+                const float rv = fmaf(dz[e], uz, fmaf(dy[e], uy, dx[e] * ux));
+                const float al = 3.0f * rv * rinv2;
+                acc[k][3] = fmaf(mr3, fmaf(-al, dx[e], ux), acc[k][3]);
+                acc[k][4] = fmaf(mr3, fmaf(-al, dy[e], uy), acc[k][4]);
+                acc[k][5] = fmaf(mr3, fmaf(-al, dz[e], uz), acc[k][5]);
+            }
     };
+    const std::integral_constant<int, 1> one{};
+    // records whose rsq form one group in the plain loops
+    constexpr int kGroup = !PRIO ? 1 : UNR >= 4 && IPT <= 2 ? 4 / IPT : UNR >= 2 && IPT <= 2 ? 2 / IPT : 1;
+    const std::integral_constant<int, kGroup> group{};
     auto fold = [&]() {
         if (PREC == 1) {
 #pragma unroll
@@ -242,7 +256,7 @@ __device__ __forceinline__ void force_block(const ForceArgs& a, float4 (*sh)[TJ 
                 const float4 q1 = jp[(size_t)j * R + 1];
                 float4 q2 = make_float4(0.f, 0.f, 0.f, 0.f);
                 if (PREC == 1) q2 = jp[(size_t)j * R + 2];
-                interact(maskc, q0, q1, q2, j);
+                interact(maskc, one, &q0, &q1, &q2, j);
             }
         };
         for (int j0 = jb; j0 < je; j0 += TJ) {
@@ -266,7 +280,7 @@ __device__ __forceinline__ void force_block(const ForceArgs& a, float4 (*sh)[TJ 
                     const float4 q1 = tile[jj * R + 1];
                     float4 q2 = make_float4(0.f, 0.f, 0.f, 0.f);
                     if (PREC == 1) q2 = tile[jj * R + 2];
-                    interact(maskc, q0, q1, q2, jt + jj);
+                    interact(maskc, one, &q0, &q1, &q2, jt + jj);
                 }
             } else if (PIPE) {
                 // software pipeline: the record of j+1 is read from LDS while
@@ -281,19 +295,23 @@ __device__ __forceinline__ void force_block(const ForceArgs& a, float4 (*sh)[TJ 
                     const float4 n1 = tile[jn * R + 1];
                     float4 n2 = make_float4(0.f, 0.f, 0.f, 0.f);
                     if (PREC == 1) n2 = tile[jn * R + 2];
-                    interact(maskc, q0, q1, q2, jt + jj);
+                    interact(maskc, one, &q0, &q1, &q2, jt + jj);
                     q0 = n0;
                     q1 = n1;
                     q2 = n2;
                 }
             } else {
-#pragma unroll UNR
-                for (int jj = 0; jj < TJ; ++jj) {
-                    const float4 q0 = tile[jj * R + 0];
-                    const float4 q1 = tile[jj * R + 1];
-                    float4 q2 = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (PREC == 1) q2 = tile[jj * R + 2];
-                    interact(maskc, q0, q1, q2, jt + jj);
+                constexpr int kRounds = UNR / kGroup > 1 ? UNR / kGroup : 1;
+#pragma unroll kRounds
+                for (int jj = 0; jj < TJ; jj += kGroup) {
+                    float4 q0[kGroup], q1[kGroup], q2[kGroup];
+#pragma unroll
+                    for (int u = 0; u < kGroup; ++u) {
+                        q0[u] = tile[(jj + u) * R + 0];
+                        q1[u] = tile[(jj + u) * R + 1];
+                        q2[u] = PREC == 1 ? tile[(jj + u) * R + 2] : make_float4(0.f, 0.f, 0.f, 0.f);
+                    }
+                    interact(maskc, group, q0, q1, q2, jt + jj);
                 }
             }
         };

@@ -434,6 +434,43 @@ hipError_t launch_predict_all(int n, const double* const* state /*x y z vx vy vz
                               const int64_t* t, const int64_t* tnext, double* const* outxv,
                               hipStream_t st);
 
+// r[k] = s[k]^-1/2 (v_rsq_f32) of a group of values at raised wave priority,
+// for loops whose other instructions are full-rate float32.  A SIMD reaches
+// that rate by issuing two waves' VALU instructions together; a quarter-rate
+// instruction in one of them throws the waves out of step, and the loop
+// falls to one instruction at a time (probe: 180 instructions with 4 v_rsq,
+// 4 waves per SIMD, 2.4 wave instructions per CU per ns; with this 4.0, as
+// without any v_rsq).  The s_setprio behind the group also fills the wait
+// state that its last result needs.  One group of four, not four of one: a
+// wave that has its SIMD for itself pays for each s_setprio (64 clusters of
+// at most 1024 bodies were 4% slower with a group a pair).  Same results,
+// start to now: 512 clusters of 64 to 8192 bodies, 4 steps, 11.4 to 10.2 ms;
+// 700 i against 65536 j 69.1 to 61.5 us; 30011 float32 bodies 638 to 600 us;
+// 40000-body leapfrog, 8 steps, 6.09 to 5.72 ms; 2^20 bodies 668 to 649 ms
+// (there the clock follows the power).  The adjoint and the latency-bound
+// j-parallel loop of small blocks gain nothing and keep the plain v_rsq.
+template <int N>
+__device__ __forceinline__ void rsq_group(float (&r)[N], const float (&s)[N]) {
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8, "group size");
+    if constexpr (N == 1)
+        asm("s_setprio 3\n\tv_rsq_f32 %0, %1\n\ts_setprio 0" : "=v"(r[0]) : "v"(s[0]));
+    else if constexpr (N == 2)
+        asm("s_setprio 3\n\tv_rsq_f32 %0, %2\n\tv_rsq_f32 %1, %3\n\ts_setprio 0"
+            : "=&v"(r[0]), "=v"(r[1])
+            : "v"(s[0]), "v"(s[1]));
+    else {
+        asm("s_setprio 3\n\tv_rsq_f32 %0, %4\n\tv_rsq_f32 %1, %5\n\tv_rsq_f32 %2, %6\n\t"
+            "v_rsq_f32 %3, %7\n\ts_setprio 0"
+            : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=v"(r[3])
+            : "v"(s[0]), "v"(s[1]), "v"(s[2]), "v"(s[3]));
+        if constexpr (N == 8)
+            asm("s_setprio 3\n\tv_rsq_f32 %0, %4\n\tv_rsq_f32 %1, %5\n\tv_rsq_f32 %2, %6\n\t"
+                "v_rsq_f32 %3, %7\n\ts_setprio 0"
+                : "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=v"(r[7])
+                : "v"(s[4]), "v"(s[5]), "v"(s[6]), "v"(s[7]));
+    }
+}
+
 // Hermite predictor (float64), Horner form of
 //   x_p = x + v D + a D^2/2 + j D^3/6,  v_p = v + a D + j D^2/2.
 __device__ __forceinline__ void predict1(double x, double v, double ac, double jk, double D,
