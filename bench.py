@@ -38,7 +38,7 @@ VALU_FILE = os.path.join(ROOT, "profiles", "force_plummer1m_valu_clock.txt")
 # the headline kernel: its tile loop, its instantiations and the rules that
 # pick its launch shape and j-split
 KERNEL_SRCS = [os.path.join(ROOT, "paper_0707_0438_amd", "csrc", f)
-               for f in ("force_block.h", "force.hip", "launch_shape.h")]
+               for f in ("force_block.h", "force.hip", "sym.hip", "launch_shape.h")]
 
 
 def log(*a):

@@ -147,7 +147,9 @@ int nbody_abi_version(void);
  * through this context is bracketed by two HIP events recorded on the
  * launch stream.  nbody_kernel_time waits for the recorded events, returns
  * the summed kernel time in milliseconds and the number of launches (HOST
- * outputs) and starts a new tally.  The events stay owned by the context. */
+ * outputs) and starts a new tally.  An evaluation in several launches (the
+ * pair-symmetric one of a large set) counts as one.  The events stay owned
+ * by the context. */
 int nbody_kernel_timing(nbody_ctx *ctx, int enable);
 int nbody_kernel_time(nbody_ctx *ctx, double *total_ms, int64_t *launches);
 
@@ -155,7 +157,8 @@ int nbody_kernel_time(nbody_ctx *ctx, double *total_ms, int64_t *launches);
  * nbody_tile; split may be 0), or clear the override when t is NULL. */
 int nbody_set_tile(nbody_ctx *ctx, nbody_prec prec, const nbody_tile *t);
 
-/* The launch shape the next nbody_force call would use for this shape. */
+/* The launch shape the next nbody_force call would use for this shape (its
+ * general kernel; see nbody_force for self-gravitating sets). */
 int nbody_get_tile(nbody_ctx *ctx, nbody_prec prec, int64_t n_i, int64_t n_j, nbody_tile *t);
 
 /* Autotuner (the number of threads per bundle is the tuning knob the paper
@@ -184,7 +187,13 @@ int nbody_autotune(nbody_ctx *ctx, hipStream_t stream, nbody_prec prec, double G
  * kernel sweeps every j (Section 3.1 counts all N^2 pairs); in the one or
  * two j-tiles that hold j = i_self[i] the pair is given zero mass, so it
  * contributes nothing to a, jerk or pot and the large self potential
- * m_i/eps never enters a float32 partial sum.  An i_self value outside
+ * m_i/eps never enters a float32 partial sum.  A DS self-gravitating set of
+ * 24576 particles or more with eps > 0 (I the same rows as J, i_self the
+ * identity, which the device checks; no pinned or tuned launch shape) is
+ * evaluated pair by pair, each pair serving both of its particles: the same
+ * float32 partial sums, added up in another order (differences of order
+ * 1e-14), from at most 2 GiB of scratch up to 2^24 particles; where that
+ * cannot be had, the general kernel runs.  An i_self value outside
  * [0, n_j) excludes nothing.  With the environment variable
  * NBODY_DEBUG_SELF_CHECK=1 set when the context is created, the call also
  * checks that each i row equals the j row i_self names (the same particle)

@@ -84,7 +84,7 @@ void* scratch_ptr(int device, hipError_t* err) {
 struct nbody_ctx {
     int device = -1;          // -1: argument-checking context without a device
     std::string err;
-    DevBuf ipack, jpack, part, sel, scratch64, vrec_i, vrec_j, vpart, integ, hist, bplan, bstate, lf;
+    DevBuf ipack, jpack, part, symflag, sel, scratch64, vrec_i, vrec_j, vpart, integ, hist, bplan, bstate, lf;
     // batched Hermite graph (captured on a context-owned stream)
     hipStream_t gstream = nullptr;
     hipEvent_t gev[2] = {nullptr, nullptr};
@@ -94,6 +94,8 @@ struct nbody_ctx {
     bool have_override[2] = {false, false};
     nbody_tile override_tile[2];
     nb::TuneCache tune;
+    int32_t sym_epoch = 0;    // calls that had i_self checked for the identity
+    bool symflag_clear = false;   // symflag holds an epoch (0 at first), not what its memory held before
     int alloc_count = 0;
     int fail_alloc_at = 0;    // debug: NBODY_DEBUG_FAIL_ALLOC=k fails the k-th allocation
     bool self_check = false;  // debug: NBODY_DEBUG_SELF_CHECK=1 verifies self rows (synchronises)
@@ -239,6 +241,21 @@ static nbody_tile pick_tile(nbody_ctx* c, int prec, int64_t ni, int64_t nj) {
     return t;
 }
 
+// Kernel timing: record the event before a pairwise launch; *end is the one
+// to record after it.
+static int timing_begin(nbody_ctx* c, hipStream_t st, hipEvent_t* end) {
+    while (c->ev.size() < c->ev_used + 2) {
+        hipEvent_t x;
+        if (hipEventCreate(&x) != hipSuccess) return set_err(c, NBODY_ERR_DEVICE, "event create");
+        c->ev.push_back(x);
+    }
+    const hipEvent_t begin = c->ev[c->ev_used];
+    *end = c->ev[c->ev_used + 1];
+    c->ev_used += 2;
+    if (hipEventRecord(begin, st) != hipSuccess) return set_err(c, NBODY_ERR_DEVICE, "event record");
+    return NBODY_OK;
+}
+
 // Core evaluation: i records (ipack, iidx) against j records (jpack).  kind 0
 // writes all 7 rows of out; kind 1 (force only) rows 0-2 and 6; kind 2 all 7
 // plus the nearest neighbour (nn, nn_r2).
@@ -246,7 +263,8 @@ static int run_force(nbody_ctx* c, hipStream_t st, int prec, double G, double ep
                      const float4* ipack, const int32_t* iidx, const int32_t* iself, int self_mode,
                      int64_t nj, const float4* jpack, double* const out[7], const nbody_tile* forced,
                      int kind = 0, int32_t* nn = nullptr, double* nn_r2 = nullptr,
-                     int* defer_split = nullptr, const FixedWS* fixed = nullptr) {
+                     int* defer_split = nullptr, const FixedWS* fixed = nullptr,
+                     const int32_t* only = nullptr) {
     if (ni == 0) return NBODY_OK;
     if (fixed && (kind != 0 || defer_split)) return set_err(c, NBODY_ERR_ARG, "fixed workspace needs kind 0");
     if (defer_split && kind != 0) return set_err(c, NBODY_ERR_ARG, "deferred split reduce needs kind 0");
@@ -303,6 +321,8 @@ static int run_force(nbody_ctx* c, hipStream_t st, int prec, double G, double ep
     if (kind == 1) a.out[3] = a.out[4] = a.out[5] = nullptr;
     a.nn = nn;
     a.nn_r2 = nn_r2;
+    a.only = only;
+    a.epoch = c->sym_epoch;
     a.partial = S > 1 ? 1 : 0;
     if (S > 1) {
         const size_t rows = kind == 2 ? 8 : 7;
@@ -317,18 +337,9 @@ static int run_force(nbody_ctx* c, hipStream_t st, int prec, double G, double ep
         }
         if (kind == 2) a.nnpart = a.part + 7 * (size_t)S * (size_t)ni;
     }
-    hipEvent_t tb = nullptr, te = nullptr;
-    if (c->timing && !fixed) {
-        while (c->ev.size() < c->ev_used + 2) {
-            hipEvent_t x;
-            if (hipEventCreate(&x) != hipSuccess) return set_err(c, NBODY_ERR_DEVICE, "event create");
-            c->ev.push_back(x);
-        }
-        tb = c->ev[c->ev_used];
-        te = c->ev[c->ev_used + 1];
-        c->ev_used += 2;
-        if (hipEventRecord(tb, st) != hipSuccess) return set_err(c, NBODY_ERR_DEVICE, "event record");
-    }
+    hipEvent_t te = nullptr;
+    if (c->timing && !fixed && !only)
+        if (int rc = timing_begin(c, st, &te)) return rc;
     hipError_t e = launch_force(prec, ipt, tj, wg, jsrc, unr, wpe, eps0, nb, S, a, st, kind);
     if (e != hipSuccess) return hip_err(c, e, "force kernel launch");
     if (te && hipEventRecord(te, st) != hipSuccess) return set_err(c, NBODY_ERR_DEVICE, "event record");
@@ -343,6 +354,8 @@ static int run_force(nbody_ctx* c, hipStream_t st, int prec, double G, double ep
         r.S = S;
         r.part = a.part;
         r.G = G;
+        r.only = only;
+        r.epoch = c->sym_epoch;
         for (int q = 0; q < 7; ++q) r.out[q] = a.out[q];
         e = launch_reduce(r, st);
         if (e != hipSuccess) return hip_err(c, e, "split reduce launch");
@@ -355,8 +368,11 @@ static int run_force(nbody_ctx* c, hipStream_t st, int prec, double G, double ep
 }
 
 static int pack_into(nbody_ctx* c, hipStream_t st, int prec, int64_t n, const nbody_src& s, bool with_m,
-                     float4* dst) {
+                     float4* dst, const int32_t* iself = nullptr) {
     PackArgs p{};
+    p.iself = iself;
+    p.bad = (int32_t*)c->symflag.p;
+    p.epoch = c->sym_epoch;
     p.n = (int)n;
     p.prec = prec;
     p.x = s.x; p.y = s.y; p.z = s.z;
@@ -369,11 +385,100 @@ static int pack_into(nbody_ctx* c, hipStream_t st, int prec, int64_t n, const nb
 }
 
 static int pack_rows(nbody_ctx* c, hipStream_t st, int prec, int64_t n, const nbody_src& s,
-                     bool with_m, DevBuf& dst) {
+                     bool with_m, DevBuf& dst, const int32_t* iself = nullptr) {
     const size_t bytes = sizeof(float4) * (size_t)rec_words(prec) * (size_t)std::max<int64_t>(n, 1);
     int rc = dev_alloc(c, dst, bytes);
     if (rc) return rc;
-    return pack_into(c, st, prec, n, s, with_m, (float4*)dst.p);
+    return pack_into(c, st, prec, n, s, with_m, (float4*)dst.p, iself);
+}
+
+// Whether one self-gravitating set takes the pair-symmetric evaluation, and
+// with which fold interval (j-tile): 0 for the general kernel.  It forms the
+// partial sums of the default tiles of 64 and 256 records, so a pinned or
+// tuned launch shape keeps the general kernel, as do float32 (one float32
+// sum over all j of a range, a serial chain), eps = 0 and softenings whose
+// square leaves the normal float32 range.
+static int sym_tile(nbody_ctx* c, int prec, double eps, int64_t n, int kind) {
+    if (prec != 1 || kind > 1 || c->have_override[prec] || n < kSymMin || n > kSymMax) return 0;
+    const float e2 = (float)(eps * eps);
+    if (!(e2 >= 1.17549435e-38f) || !isfinite(e2)) return 0;
+    nbody_tile t;
+    if (kind == 0 && c->tune.lookup(prec, n, n, &t)) return 0;
+    const int tj = default_tile_kind(kind, prec, n, n).tile_j;
+    return tj == 64 || tj == 256 ? tj : 0;
+}
+
+// Split-partial bytes of the general kernel for a direct call (eps > 0).
+static size_t direct_part_bytes(nbody_ctx* c, int prec, int64_t ni, int64_t nj, int kind) {
+    nbody_tile t = kind == 0 || c->have_override[prec] ? pick_tile(c, prec, ni, nj)
+                                                       : default_tile_kind(kind, prec, ni, nj);
+    if (t.split <= 0) t.split = choose_split(ni, nj, t);
+    int nb, S, jc;
+    split_plan(ni, nj, t.wg * t.ipt, t.tile_j, t.split, &nb, &S, &jc);
+    return S > 1 ? sizeof(float2) * 8 * (size_t)S * (size_t)ni : 0;
+}
+
+// Pair-symmetric evaluation of the n packed records; *done = false when its
+// rows do not fit in memory (the caller then takes the general kernel).
+// check: only if the pack pass found i_self to be the identity.
+static int run_sym(nbody_ctx* c, hipStream_t st, int tj, int kind, double G, double eps, int64_t n,
+                   const float4* pack, double* const out[7], bool check, bool* done) {
+    const int nq = kind == 1 ? 4 : 7;
+    const SymShape s = sym_shape(n, tj, nq);
+    *done = false;
+    // (with the check, room for the general kernel's partials too: it is
+    // launched behind, into the same buffer)
+    const size_t need = std::max(s.bytes, check ? direct_part_bytes(c, 1, n, n, kind) : 0);
+    if (dev_alloc(c, c->part, need) != NBODY_OK) {
+        c->err.clear();
+        return NBODY_OK;
+    }
+    *done = true;
+    SymArgs a{};
+    a.pack = pack;
+    a.n = (int)n;
+    a.ns = (int)sym_stride(n);
+    a.eps2 = (float)(eps * eps);
+    a.nb = s.nb;
+    a.lb = s.lb;
+    a.lbs = s.lbs;
+    a.lp = s.lp;
+    a.G = G;
+    a.bad = check ? (const int32_t*)c->symflag.p : nullptr;
+    a.epoch = c->sym_epoch;
+    a.own = (double*)c->part.p;
+    a.partner = a.own + (size_t)s.np * nq * (size_t)a.ns;
+    const int order[7] = {0, 1, 2, 6, 3, 4, 5};
+    for (int q = 0; q < nq; ++q) a.out[q] = out[order[q]];
+    hipEvent_t te = nullptr;   // the bands of one evaluation count as one launch
+    if (c->timing)
+        if (int rc = timing_begin(c, st, &te)) return rc;
+    for (int d0 = 0; d0 < s.dists; d0 += s.nd) {
+        const int d1 = std::min(s.dists, d0 + s.nd);
+        a.off0 = d0 << s.lbs;
+        a.off1 = d1 << s.lbs;
+        a.first = d0 == 0;
+        a.last = d1 == s.dists;
+        a.half = a.last && s.nb % 2 == 0;
+        const int items = (a.off1 - a.off0 + s.lp - 1) / s.lp * s.nb;
+        hipError_t e = launch_sym(tj, kind, items, a, st);
+        if (e != hipSuccess) return hip_err(c, e, "symmetric force launch");
+        if (a.last && te && hipEventRecord(te, st) != hipSuccess) return set_err(c, NBODY_ERR_DEVICE, "event record");
+        e = launch_sym_reduce(kind, a, st);
+        if (e != hipSuccess) return hip_err(c, e, "symmetric reduce launch");
+    }
+    return NBODY_OK;
+}
+
+// a, jerk (kind 0) and potential of one packed set, self excluded.
+static int run_self(nbody_ctx* c, hipStream_t st, int prec, double G, double eps, int64_t n, const float4* pack,
+                    double* const out[7], int kind = 0) {
+    if (const int tj = sym_tile(c, prec, eps, n, kind)) {
+        bool done;
+        const int rc = run_sym(c, st, tj, kind, G, eps, n, pack, out, false, &done);
+        if (rc || done) return rc;
+    }
+    return run_force(c, st, prec, G, eps, n, pack, nullptr, nullptr, 2, n, pack, out, nullptr, kind);
 }
 
 static bool same_src(const nbody_src& a, const nbody_src& b) {
@@ -395,6 +500,47 @@ static int debug_self_check(nbody_ctx* c, hipStream_t st, int prec, int64_t ni, 
     if (e != hipSuccess) return hip_err(c, e, "self check");
     if (h) return set_err(c, NBODY_ERR_ARG, "i_self: %d i rows differ from their j rows or index beyond n_j", h);
     return NBODY_OK;
+}
+
+// The direct calls: pack both sets and evaluate.  When the i set is the j
+// set and i_self the identity (checked on the device by the pack pass), the
+// pair-symmetric evaluation; the general kernel is launched behind it and
+// leaves at once unless the check failed.
+static int force_rows(nbody_ctx* c, hipStream_t st, int p, double G, double eps, int64_t n_i, const nbody_src& I,
+                      const int32_t* i_self, int64_t n_j, const nbody_src& J, double* const out[7], int kind,
+                      int32_t* nn, double* nn_r2) {
+    const bool own = n_i == n_j && same_src(I, J);
+    int tj = own && i_self ? sym_tile(c, p, eps, n_i, kind) : 0;
+    if (tj && dev_alloc(c, c->symflag, 256) != NBODY_OK) {
+        c->err.clear();
+        tj = 0;
+    }
+    if (tj) {
+        if (!c->symflag_clear) {
+            const hipError_t e = launch_fill_i32((int*)c->symflag.p, 64, 0, st);
+            if (e != hipSuccess) return hip_err(c, e, "flag clear");
+            c->symflag_clear = true;
+        }
+        c->sym_epoch = c->sym_epoch == INT32_MAX ? 1 : c->sym_epoch + 1;
+    }
+    int rc = pack_rows(c, st, p, n_j, J, true, c->jpack, tj ? i_self : nullptr);
+    if (rc) return rc;
+    const float4* ip = (const float4*)c->jpack.p;
+    if (!own) {
+        rc = pack_rows(c, st, p, n_i, I, false, c->ipack);
+        if (rc) return rc;
+        ip = (const float4*)c->ipack.p;
+    }
+    if ((rc = debug_self_check(c, st, p, n_i, ip, i_self, n_j, (const float4*)c->jpack.p))) return rc;
+    const int32_t* only = nullptr;
+    if (tj) {
+        bool done;
+        rc = run_sym(c, st, tj, kind, G, eps, n_i, ip, out, true, &done);
+        if (rc) return rc;
+        if (done) only = (const int32_t*)c->symflag.p;
+    }
+    return run_force(c, st, p, G, eps, n_i, ip, nullptr, i_self, 0, n_j, (const float4*)c->jpack.p, out, nullptr,
+                     kind, nn, nn_r2, nullptr, nullptr, only);
 }
 
 extern "C" {
@@ -491,6 +637,14 @@ static int need_device(nbody_ctx* c) {
 static size_t reserve_part_bytes(nbody_ctx* c, int64_t max_i, int64_t max_j) {
     const int64_t ni = std::max<int64_t>(max_i, 1), nj = std::max<int64_t>(max_j, 1);
     size_t part = 0;
+    // pair-symmetric rows of every self-gravitating set up to the smaller
+    // count; beyond 2^18 particles they fill their limit, or grow with n
+    const int64_t ns = std::min(std::min(ni, nj), kSymMax);
+    if (ns >= kSymMin && !c->have_override[1]) {
+        for (int64_t n = kSymMin; n < std::min<int64_t>(ns + kSymGroup, 1 << 18); n += kSymGroup)
+            part = std::max(part, sym_shape(std::min(n, ns), default_tile(1, n, n).tile_j, 7).bytes);
+        if (ns >= (1 << 18)) part = std::max({part, (size_t)kSymBytes, sym_shape(ns, 256, 7).bytes});
+    }
     for (int prec = 0; prec < 2; ++prec) {
         int64_t n = ni;
         for (;;) {
@@ -518,6 +672,7 @@ int nbody_reserve(nbody_ctx* c, int64_t max_i, int64_t max_j) {
     int rc = dev_alloc(c, c->ipack, sizeof(float4) * kRecDS * ni);
     if (!rc) rc = dev_alloc(c, c->jpack, sizeof(float4) * kRecDS * nj);
     if (!rc && part > 0) rc = dev_alloc(c, c->part, part);
+    if (!rc && std::min(max_i, max_j) >= kSymMin) rc = dev_alloc(c, c->symflag, 256);
     return rc;
 }
 
@@ -610,18 +765,8 @@ int nbody_force(nbody_ctx* c, hipStream_t st, nbody_prec prec, double G, double 
     DeviceGuard g(c->device);
     if (!g.ok) return set_err(c, NBODY_ERR_DEVICE, "hipSetDevice(%d) failed", c->device);
     const int p = (int)prec;
-    int rc = pack_rows(c, st, p, n_j, J, true, c->jpack);
-    if (rc) return rc;
-    const float4* ip = (const float4*)c->jpack.p;
-    if (!(n_i == n_j && same_src(I, J))) {
-        rc = pack_rows(c, st, p, n_i, I, false, c->ipack);
-        if (rc) return rc;
-        ip = (const float4*)c->ipack.p;
-    }
-    if ((rc = debug_self_check(c, st, p, n_i, ip, i_self, n_j, (const float4*)c->jpack.p))) return rc;
     double* o[7] = {out.ax, out.ay, out.az, out.jx, out.jy, out.jz, out.pot};
-    return run_force(c, st, p, G, eps, n_i, ip, nullptr, i_self, 0, n_j, (const float4*)c->jpack.p, o,
-                     nullptr);
+    return force_rows(c, st, p, G, eps, n_i, I, i_self, n_j, J, o, 0, nullptr, nullptr);
 }
 
 int nbody_force_noalloc(nbody_ctx* c, hipStream_t st, nbody_prec prec, double G, double eps, int64_t n_i,
@@ -697,19 +842,9 @@ static int force_kind(nbody_ctx* c, hipStream_t st, nbody_prec prec, double G, d
         J.vx = J.vy = J.vz = nullptr;
     }
     const int p = (int)prec;
-    int rc = pack_rows(c, st, p, n_j, J, true, c->jpack);
-    if (rc) return rc;
-    const float4* ip = (const float4*)c->jpack.p;
-    if (!(n_i == n_j && same_src(I, J))) {
-        rc = pack_rows(c, st, p, n_i, I, false, c->ipack);
-        if (rc) return rc;
-        ip = (const float4*)c->ipack.p;
-    }
-    if ((rc = debug_self_check(c, st, p, n_i, ip, i_self, n_j, (const float4*)c->jpack.p))) return rc;
     double* o[7] = {out.ax, out.ay, out.az, vel ? out.jx : nullptr, vel ? out.jy : nullptr,
                     vel ? out.jz : nullptr, out.pot};
-    return run_force(c, st, p, G, eps, n_i, ip, nullptr, i_self, 0, n_j, (const float4*)c->jpack.p, o, nullptr,
-                     kind, nn, nn_r2);
+    return force_rows(c, st, p, G, eps, n_i, I, i_self, n_j, J, o, kind, nn, nn_r2);
 }
 
 int nbody_force_acc(nbody_ctx* c, hipStream_t st, nbody_prec prec, double G, double eps, int64_t n_i,
@@ -755,7 +890,7 @@ int nbody_leapfrog(nbody_ctx* c, hipStream_t st, nbody_prec prec, double G, doub
     double* const prow = pot ? pot : pot_s;
     auto eval = [&](double* a3) {
         double* o[7] = {a3, a3 + n, a3 + 2 * n, nullptr, nullptr, nullptr, prow};
-        return run_force(c, st, p, G, eps, n, jp, nullptr, nullptr, 2, n, jp, o, nullptr, 1);
+        return run_self(c, st, p, G, eps, n, jp, o, 1);
     };
     nbody_src P{x, x + n, x + 2 * n, nullptr, nullptr, nullptr, m};
     if (!have_acc || (nsteps == 0 && pot)) {
@@ -921,8 +1056,7 @@ int nbody_hermite_set_state(nbody_hermite* h, hipStream_t st, nbody_src P) {
     int rc = pack_rows(c, st, p, h->n, state_src(h), true, c->jpack);
     if (rc) return rc;
     double* o[7] = {h->s[6], h->s[7], h->s[8], h->s[9], h->s[10], h->s[11], h->f[6]};
-    rc = run_force(c, st, p, h->o.G, h->o.eps, h->n, (const float4*)c->jpack.p, nullptr, nullptr, 2,
-                   h->n, (const float4*)c->jpack.p, o, nullptr);
+    rc = run_self(c, st, p, h->o.G, h->o.eps, h->n, (const float4*)c->jpack.p, o);
     if (rc) return rc;
     InitDtArgs a{};
     a.n = (int)h->n;
@@ -1141,7 +1275,12 @@ static int hermite_step_shared(nbody_hermite* h, hipStream_t st, int64_t t_limit
         hipError_t e = launch_blk_step(p, h->o.eps == 0.0, a, st);
         if (e != hipSuccess) return hip_err(c, e, "force launch");
     } else {
-        int rc = run_force(c, st, p, h->o.G, h->o.eps, n, h->spack, nullptr, nullptr, 2, n, h->spack, h->f, nullptr,
+        bool done = false;
+        int rc = NBODY_OK;
+        if (const int tj = sym_tile(c, p, h->o.eps, n, 0))
+            rc = run_sym(c, st, tj, 0, h->o.G, h->o.eps, n, h->spack, h->f, false, &done);
+        if (!rc && !done)
+            rc = run_force(c, st, p, h->o.G, h->o.eps, n, h->spack, nullptr, nullptr, 2, n, h->spack, h->f, nullptr,
                            0, nullptr, nullptr, &S);
         if (rc) return rc;
     }
@@ -1457,8 +1596,7 @@ int nbody_hermite_energy(nbody_hermite* h, hipStream_t st, double* ekin, double*
     int rc = pack_rows(c, st, p, n, P, true, c->jpack);
     if (rc) return rc;
     double* o[7] = {h->f[0], h->f[1], h->f[2], h->f[3], h->f[4], h->f[5], h->f[6]};
-    rc = run_force(c, st, p, h->o.G, h->o.eps, n, (const float4*)c->jpack.p, nullptr, nullptr, 2, n,
-                   (const float4*)c->jpack.p, o, nullptr);
+    rc = run_self(c, st, p, h->o.G, h->o.eps, n, (const float4*)c->jpack.p, o);
     if (rc) return rc;
     e = launch_energy(n, h->pred[3], h->pred[4], h->pred[5], h->s[12], h->f[6], h->e2, st);
     if (e != hipSuccess) return hip_err(c, e, "energy launch");
@@ -1714,8 +1852,7 @@ static int shared_force(nbody_ctx* c, hipStream_t st, int prec, double G, double
     int rc = pack_rows(c, st, prec, n, rows_src(x, v, m, n), true, c->jpack);
     if (rc) return rc;
     double* o[7] = {a3, a3 + n, a3 + 2 * n, j3, j3 + n, j3 + 2 * n, pot};
-    return run_force(c, st, prec, G, eps, n, (const float4*)c->jpack.p, nullptr, nullptr, 2, n,
-                     (const float4*)c->jpack.p, o, nullptr);
+    return run_self(c, st, prec, G, eps, n, (const float4*)c->jpack.p, o);
 }
 
 // One step from (w.x, w.v, w.a, w.j); the predicted state goes to xp, vp.

@@ -53,6 +53,7 @@ void force_kernel(ForceArgs a) {
     constexpr bool LOW = unr_low(UNR);
     __shared__ float4 sh[LOW ? 1 : 2][TJ * Rec<PREC>::R];
     __shared__ float losh[LOW && PREC == 1 ? 7 * IPT * WG : 1];
+    if (a.only && *a.only != a.epoch) return;
     const int jb = blockIdx.y * a.jchunk;
     const int je = min(a.nj, jb + a.jchunk);
     force_block<PREC, IPT, TJ, WG, EPS0, false, unr_depth(UNR), unr_pipe(UNR), 0, LOW, PRIO>(
@@ -63,6 +64,7 @@ void force_kernel(ForceArgs a) {
 template <int PREC, int KIND, int IPT, int TJ, int WG, bool EPS0, int UNR, bool PRIO>
 __global__ __launch_bounds__(WG) void force_kernel_kind(ForceArgs a) {
     __shared__ float4 sh[2][TJ * Rec<PREC>::R];
+    if (a.only && *a.only != a.epoch) return;
     const int jb = blockIdx.y * a.jchunk;
     const int je = min(a.nj, jb + a.jchunk);
     force_block<PREC, IPT, TJ, WG, EPS0, false, unr_depth(UNR), unr_pipe(UNR), KIND, false, PRIO>(
@@ -139,6 +141,7 @@ __device__ __forceinline__ double reduce_finish(const ReduceArgs& a, int q, doub
 }
 
 __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
+    if (a.only && *a.only != a.epoch) return;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= 7 * (int64_t)a.ni) return;
     const int q = (int)(t / a.ni);
@@ -154,6 +157,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
 }
 
 __global__ __launch_bounds__(256) void reduce_wave_kernel(ReduceArgs a) {
+    if (a.only && *a.only != a.epoch) return;
     const int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int lane = threadIdx.x & 63;
     if (w >= 7 * (int64_t)a.ni) return;   // whole waves leave together

@@ -32,6 +32,8 @@ struct ForceArgs {
     int32_t* nn;            // nearest-neighbour evaluation: j index per i (final mode)
     double* nn_r2;          //   and its squared distance (final mode; NULL: not wanted)
     float2* nnpart;         //   [S][ni] (r^2, j bits) per range (partial mode)
+    const int32_t* only;    // direct launches: run only when *only == epoch (NULL: always)
+    int32_t epoch;
 };
 
 constexpr float kPadPos = 1.0e18f;   // far-away position of padding records

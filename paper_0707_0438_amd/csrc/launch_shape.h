@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "nbody.h"
 
@@ -104,6 +105,61 @@ inline nbody_tile default_tile_kind(int kind, int prec, int64_t ni, int64_t nj) 
     // the full evaluation's default (two i per lane for DS at large sizes) is
     // also the fastest force-only and neighbour shape of the sweeps
     return default_tile(prec, ni, nj, kind == 0);
+}
+
+// Shape of the pair-symmetric evaluation of n particles (sym.hip): blocks of
+// lb particles, bands of nd block distances, each block's stretch of a band
+// in np pieces of lp.  tj: the j-tile whose partial sums it forms (64 or 256).
+struct SymShape {
+    int nb, lb, lbs, nd, np, lp;
+    int dists;          // distances 0 .. nb / 2
+    size_t bytes;       // float64 rows of one launch
+};
+// The rows of one launch stay within this many bytes.
+constexpr int64_t kSymBytes = (int64_t)1 << 31;
+constexpr int kSymGroup = 1024;      // i-particles a work-group holds at a time
+constexpr int kSymResident = 1024;   // work-groups on the chip at once: four per CU
+constexpr int64_t kSymMin = 24576;   // 20001 bodies: 344 us against the general kernel's 291; 26000: 488 against 526
+constexpr int64_t kSymMax = (int64_t)1 << 29;
+// rows are padded to whole groups, so a shape depends on n by its groups only
+constexpr int64_t sym_stride(int64_t n) { return (n + kSymGroup - 1) / kSymGroup * kSymGroup; }
+inline SymShape sym_shape(int64_t n, int tj, int quantities) {
+    SymShape best{};
+    double best_t = 0.0;
+    const int64_t row = 8 * (int64_t)quantities * sym_stride(n);
+    for (int g = 0; g < 4; ++g) {
+        SymShape s;
+        s.lbs = 10 + g;
+        s.lb = 1 << s.lbs;
+        s.nb = (int)((n + s.lb - 1) >> s.lbs);
+        s.dists = s.nb / 2 + 1;
+        int last_np = 0;
+        for (int r = 1; r <= 8; ++r) {
+            // about r rounds of work-groups
+            const int np = std::max(1, r * kSymResident / s.nb);
+            if (np == last_np) continue;
+            last_np = np;
+            const int64_t most = std::max<int64_t>(1, kSymBytes / row - np);
+            const int bands = (int)((s.dists + most - 1) / most);
+            s.nd = (s.dists + bands - 1) / bands;
+            const int64_t len = (int64_t)s.nd << s.lbs;
+            s.lp = (int)(((len + np - 1) / np + tj - 1) / tj * tj);
+            s.np = (int)((len + s.lp - 1) / s.lp);
+            s.bytes = (size_t)row * (size_t)(s.nd + s.np);
+            // time in steps of a work-group (about 1 us): whole rounds of
+            // items, and a third of a round for the CUs' unequal pace (2^17
+            // bodies: 9.3 ms in one round, 8.2 ms in seven); the rows' way
+            // through memory
+            const double rounds = std::max(1.0, std::ceil((double)s.nb * s.np / kSymResident));
+            const double t = bands * ((rounds + 0.35) * (1 << g) * (s.lp + tj / 4 + 40) +
+                                      (double)row * (s.nd + s.np) / 2.5e6 + 5);
+            if (best_t == 0.0 || t < best_t) {
+                best_t = t;
+                best = s;
+            }
+        }
+    }
+    return best;
 }
 
 }  // namespace nb

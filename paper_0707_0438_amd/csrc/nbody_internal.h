@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "launch_shape.h"
 
 namespace nb {
@@ -239,6 +241,8 @@ struct ReduceArgs {
     double G;
     double* out[7];
     const DevPlan* plan;    // plan-driven launch: ni and S come from here
+    const int32_t* only;    // run only when *only == epoch (NULL: always)
+    int32_t epoch;
 };
 
 // Launch the pairwise kernel for one configuration; returns hipError_t.
@@ -255,6 +259,25 @@ bool force_variant_at(int k, int* prec, int* ipt, int* tj, int* wg, int* jsrc, i
                       int* kind);
 // Rows of ReduceArgs.out that are NULL are skipped.
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st);
+
+// Pair-symmetric sums of one self-gravitating set (sym.hip).
+struct SymArgs {
+    const float4* pack;     // DS records of all n particles
+    int n, ns;              // ns: row stride of own and partner (multiple of 4)
+    float eps2;
+    int nb, lb, lbs;        // blocks of lb = 2^lbs particles
+    int off0, off1, lp;     // this launch: ring offsets from a block's start, in pieces of lp
+    int half;               // off1 closes the distance nb / 2, nb even: blocks from nb / 2 on stop lb before
+    int first, last;        // reduction: first / last band of distances
+    double G;
+    const int32_t* bad;     // *bad == epoch: i_self is not the identity, leave (NULL: it is)
+    int32_t epoch;
+    double* own;            // [pieces][quantities][ns]
+    double* partner;        // [block distances][quantities][ns]
+    double* out[7];         // ax ay az pot jx jy jz
+};
+hipError_t launch_sym(int tile_j, int kind, int items, const SymArgs& a, hipStream_t st);
+hipError_t launch_sym_reduce(int kind, const SymArgs& a, hipStream_t st);
 hipError_t launch_nn_reduce(int ni, int S, const float2* nnpart, int32_t* nn, double* nn_r2, hipStream_t st);
 // Leapfrog: v += a h, x += v dt, then pack x (and m) into j records; and v += a h.
 hipError_t launch_lf_kick_drift_pack(int prec, int n, double* x, double* v, const double* acc, const double* m,
@@ -299,6 +322,10 @@ struct PackArgs {
     const int64_t* tnext;                          // device scalar (NULL: use tn)
     int64_t tn;                                    // block time when tnext is NULL
     float4* out;
+    // launch_pack: *bad = epoch when iself (if given) is not the identity
+    const int32_t* iself;
+    int32_t* bad;
+    int32_t epoch;
 };
 hipError_t launch_pack(const PackArgs& a, hipStream_t st);
 // Debug: *bad = number of i rows whose self index names a j record that is

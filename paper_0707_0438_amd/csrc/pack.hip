@@ -12,6 +12,7 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs a) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
     pack_one<PREC>(a, k, a.t ? (a.tnext ? *a.tnext : a.tn) : 0);
+    if (a.iself && a.iself[k] != k) *a.bad = a.epoch;
 }
 
 hipError_t launch_pack(const PackArgs& a, hipStream_t st) {

@@ -1,0 +1,24 @@
+"""Host logic of the pair-symmetric evaluation (no GPU): its launch shapes
+cover every pair of blocks once, within the scratch asked for.  A small host
+program compiled against the library's internal header."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_0707_0438_amd", "csrc")
+
+
+@pytest.mark.timeout(300)
+def test_shapes_cover_every_pair_of_blocks(tmp_path):
+    from paper_0707_0438_amd import build
+    exe = str(tmp_path / "sym_shape")
+    cmd = [build.hipcc(), "-O2", "-std=c++17", "-x", "hip", f"--offload-arch={build.ARCH}",
+           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+           os.path.join(ROOT, "tests", "host", "sym_shape.cpp"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=240)
+    assert r.returncode == 0, r.stdout[-2000:]
