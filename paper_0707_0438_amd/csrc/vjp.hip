@@ -242,20 +242,41 @@ __global__ __launch_bounds__(kVjpWG) void vjp_kernel(VjpArgs a) {
     }
 }
 
-__global__ __launch_bounds__(256) void vjp_reduce_kernel(VjpArgs a, int S) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= a.nl) return;
+// Split reduce: 64 particles a work-group, a wave a quantity, so that a small
+// set still has nine waves' loads in flight per 64 particles (N = 16384, 32
+// ranges, 38 MB: 7.6 us, with a thread per particle 74).  Each sum
+// runs over the ranges in order.
+__global__ __launch_bounds__(64 * kVjpAcc) void vjp_reduce_kernel(VjpArgs a, int S) {
+    __shared__ double sum[kVjpAcc][64];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int k = blockIdx.x * 64 + lane;
+    if (k < a.nl) {
+        const float2* p = a.part + (size_t)q * a.nl + k;
+        const size_t step = (size_t)kVjpAcc * a.nl;
+        double s = 0.0;
+        int sp = 0;
+        for (; sp + 8 <= S; sp += 8) {
+            float2 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = p[(size_t)(sp + u) * step];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                s += (double)v[u].x;
+                s += (double)v[u].y;
+            }
+        }
+        for (; sp < S; ++sp) {
+            const float2 v = p[(size_t)sp * step];
+            s += (double)v.x;
+            s += (double)v.y;
+        }
+        sum[q][lane] = s;
+    }
+    __syncthreads();
+    if (q != 0 || k >= a.nl) return;
     double v[kVjpAcc];
 #pragma unroll
-    for (int q = 0; q < kVjpAcc; ++q) {
-        double s = 0.0;
-        for (int sp = 0; sp < S; ++sp) {
-            const float2 p = a.part[((size_t)sp * kVjpAcc + q) * a.nl + k];
-            s += (double)p.x;
-            s += (double)p.y;
-        }
-        v[q] = s;
-    }
+    for (int c = 0; c < kVjpAcc; ++c) v[c] = sum[c][lane];
     vjp_finish(a, k, v);
 }
 
@@ -278,7 +299,7 @@ hipError_t launch_vjp(int prec, bool own, bool partner, int S, const VjpArgs& a,
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !a.part) return e;
-    hipLaunchKernelGGL(vjp_reduce_kernel, dim3((a.nl + 255) / 256), dim3(256), 0, st, a, S);
+    hipLaunchKernelGGL(vjp_reduce_kernel, dim3((a.nl + 63) / 64), dim3(64 * kVjpAcc), 0, st, a, S);
     return hipGetLastError();
 }
 
