@@ -237,7 +237,7 @@ static nbody_tile pick_tile(nbody_ctx* c, int prec, int64_t ni, int64_t nj) {
     } else if (!c->tune.lookup(prec, ni, nj, &t)) {
         t = default_tile(prec, ni, nj);
     }
-    if (t.split <= 0) t.split = choose_split(ni, nj, t);
+    if (t.split <= 0) t.split = choose_split(prec, ni, nj, t);
     return t;
 }
 
@@ -276,7 +276,7 @@ static int run_force(nbody_ctx* c, hipStream_t st, int prec, double G, double ep
     } else {
         t = default_tile_kind(kind, prec, ni, nj);
     }
-    if (t.split <= 0) t.split = choose_split(ni, nj, t);
+    if (t.split <= 0) t.split = choose_split(prec, ni, nj, t, kind);
     const bool eps0 = eps == 0.0;
     int ipt = t.ipt, tj = t.tile_j, wg = t.wg, jsrc = t.jsrc, unr = t.unroll, wpe = t.waves;
     if (!force_variant_exists(prec, ipt, tj, wg, jsrc, unr, wpe, eps0, kind)) {
@@ -412,7 +412,7 @@ static int sym_tile(nbody_ctx* c, int prec, double eps, int64_t n, int kind) {
 static size_t direct_part_bytes(nbody_ctx* c, int prec, int64_t ni, int64_t nj, int kind) {
     nbody_tile t = kind == 0 || c->have_override[prec] ? pick_tile(c, prec, ni, nj)
                                                        : default_tile_kind(kind, prec, ni, nj);
-    if (t.split <= 0) t.split = choose_split(ni, nj, t);
+    if (t.split <= 0) t.split = choose_split(prec, ni, nj, t, kind);
     int nb, S, jc;
     split_plan(ni, nj, t.wg * t.ipt, t.tile_j, t.split, &nb, &S, &jc);
     return S > 1 ? sizeof(float2) * 8 * (size_t)S * (size_t)ni : 0;
@@ -2354,7 +2354,7 @@ int nbody_autotune(nbody_ctx* c, hipStream_t st, nbody_prec prec, double G, doub
             {
                 nbody_tile t = cand[ci];
 
-                t.split = choose_split(n_i, n_j, t);
+                t.split = choose_split(p, n_i, n_j, t);
                 rc = run_force(c, st, p, G, eps, n_i, ip, nullptr, nullptr, 0, n_j, (const float4*)c->jpack.p, o, &t);
                 if (rc) break;
                 hipError_t e = hipEventRecord(e0, st);

@@ -59,9 +59,20 @@ constexpr int64_t kLongTiles = 64;
 // The long-evaluation split keeps its partial sums (8 rows of 8 bytes per
 // i and range at most) within this many bytes.
 constexpr int64_t kLongPartBytes = (int64_t)1 << 31;
-inline int choose_split(int64_t ni, int64_t nj, const nbody_tile& t) {
+inline int choose_split(int prec, int64_t ni, int64_t nj, const nbody_tile& t, int kind = 0) {
     int nb, S, jc;
     split_plan(ni, nj, t.wg * t.ipt, t.tile_j, 0, &nb, &S, &jc);
+    // 64-record tiles, DS: twice the work-groups of split_plan as long as a
+    // range keeps five tiles: more than the chip holds at once, so the CUs
+    // fill up evenly.  One round depends on how the dispatcher happens to
+    // spread it (N = 16384, 2048 work-groups: 201 or 231 us by which kernel
+    // ran before; 4096: 204).  N = 23000 435 to 390 us, 12000 i against 65536
+    // j 646 to 587; N = 8192, two tiles a range, would lose 4%.  The other
+    // kinds' shorter loops gain from 24 tiles a range on only (force-only,
+    // N = 20001, 23 tiles: 184 to 196 us).  Float32 keeps its ranges: each is
+    // one float32 sum.
+    if (prec == 1 && t.tile_j == 64 && nb > 0 && (kind == 0 || jc >= 24 * t.tile_j))
+        S = (int)std::max<int64_t>(S, std::min<int64_t>((4096 + nb - 1) / nb, nj / (5 * t.tile_j)));
     const int64_t per = (int64_t)t.wg * t.ipt;
     const int64_t nbl = (ni + per - 1) / per;
     int64_t Sl = nbl > 0 ? (kLongWG + nbl - 1) / nbl : 1;
