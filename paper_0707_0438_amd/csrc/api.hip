@@ -2005,11 +2005,18 @@ static nbody_tile batched_tile(nbody_ctx* c, int prec, int64_t n_total, int32_t 
     if (c->have_override[prec]) {
         t = c->override_tile[prec];
     } else if (!c->tune.lookup(prec + 2, n_total, n_clusters, &t)) {
-        t.tile_j = 64;
+        // 256 lanes where that still gives every CU many work-groups, 128
+        // for fewer, which then end closer together (512 clusters of 64 to
+        // 8192 bodies, 6800 groups of 128: 2.74 to 2.65 ms DS, 2.46 to 2.21
+        // float32; 64 clusters, 850 groups: 0.76 against 0.77 and 0.68
+        // against 0.70)
+        t.tile_j = 128;
         t.ipt = 1;
-        t.wg = 128;
+        t.wg = n_total >= 4096 * 128 ? 256 : 128;
         t.split = 1;
         t.jsrc = 0;
+        t.unroll = 0;
+        t.waves = 0;
     }
     if (t.jsrc != 0 || t.unroll != 0 || t.waves != 0 || !force_variant_exists(prec, t.ipt, t.tile_j, t.wg, 0, 4, 0, false)) {
         t.tile_j = 128;

@@ -223,9 +223,10 @@ inline int64_t blk_part_rows(int64_t n, int prec) {
 }
 
 // waves per SIMD asked of the compiler for blk_step_kernel (a register cap:
-// the large-block tile loop keeps the occupancy of its direct-launch form)
+// four records in flight take more than the 96 registers of five waves; five
+// made the 65536-body run 5% longer)
 #ifndef NB_BLK_STEP_WAVES
-#define NB_BLK_STEP_WAVES 5
+#define NB_BLK_STEP_WAVES 4
 #endif
 constexpr int kBlkStepWaves = NB_BLK_STEP_WAVES;
 // 1: the block-step front end runs as one launch (launch_blk_front_fused)
