@@ -157,12 +157,12 @@ inline SymShape sym_shape(int64_t n, int tj, int quantities) {
             s.lp = (int)(((len + np - 1) / np + tj - 1) / tj * tj);
             s.np = (int)((len + s.lp - 1) / s.lp);
             s.bytes = (size_t)row * (size_t)(s.nd + s.np);
-            // time in steps of a work-group (about 1 us): whole rounds of
-            // items, and a third of a round for the CUs' unequal pace (2^17
-            // bodies: 9.3 ms in one round, 8.2 ms in seven); the rows' way
-            // through memory
-            const double rounds = std::max(1.0, std::ceil((double)s.nb * s.np / kSymResident));
-            const double t = bands * ((rounds + 0.35) * (1 << g) * (s.lp + tj / 4 + 40) +
+            // time in steps of a work-group (about 1 us): rounds of items and
+            // most of another for the CUs' unequal pace (2^17 bodies: 9.3 ms
+            // in one round, 8.2 in seven; 40000, force only: 0.69 ms in two,
+            // 0.66 in three and a third); the rows' way through memory
+            const double rounds = std::max(1.0, (double)s.nb * s.np / kSymResident);
+            const double t = bands * ((rounds + 0.8) * (1 << g) * (s.lp + tj / 4 + 40) +
                                       (double)row * (s.nd + s.np) / 2.5e6 + 5);
             if (best_t == 0.0 || t < best_t) {
                 best_t = t;
