@@ -672,7 +672,7 @@ def main():
             "unit": "TFLOP/s",
             "frac": round(achieved / FP32_PEAK_TFLOPS, 4),
             "traffic": traffic,
-            "kernel": "force_kernel (pairwise acc+jerk+pot)",
+            "kernel": ("sym_kernel" if args.prec == "ds" else "force_kernel") + " (pairwise acc+jerk+pot)",
             "kernel_ms": round(k_ms, 3),
             "launches": r["launches"],
         },

@@ -188,12 +188,12 @@ int nbody_autotune(nbody_ctx *ctx, hipStream_t stream, nbody_prec prec, double G
  * two j-tiles that hold j = i_self[i] the pair is given zero mass, so it
  * contributes nothing to a, jerk or pot and the large self potential
  * m_i/eps never enters a float32 partial sum.  A DS self-gravitating set of
- * 24576 particles or more with eps > 0 (I the same rows as J, i_self the
+ * 24576 to 2^24 particles with eps > 0 (I the same rows as J, i_self the
  * identity, which the device checks; no pinned or tuned launch shape) is
  * evaluated pair by pair, each pair serving both of its particles: the same
  * float32 partial sums, added up in another order (differences of order
- * 1e-14), from at most 2 GiB of scratch up to 2^24 particles; where that
- * cannot be had, the general kernel runs.  An i_self value outside
+ * 1e-14), with at most 2 GiB of scratch; where that cannot be had, the
+ * general kernel runs.  An i_self value outside
  * [0, n_j) excludes nothing.  With the environment variable
  * NBODY_DEBUG_SELF_CHECK=1 set when the context is created, the call also
  * checks that each i row equals the j row i_self names (the same particle)

@@ -18,13 +18,13 @@
 // both float32 partial sums run over exactly the 4 ROW = TJ consecutive
 // partners, in the order, that a j-tile of the general kernel has: the
 // partial sums are the general kernel's bit for bit, and only the sums over
-// tiles (compensated there, two-sum and float64 here) are formed in another
-// order.  ROW = 16 (DPP row), 32 or 64 lanes gives TJ = 64, 128 or 256.
+// tiles (a two-sum there, float64 here) are formed in another order.  ROW =
+// 16 (a DPP row, four chains a wave) or 64 lanes gives TJ = 64 or 256.
 //
 // The skew costs ROW steps per stream to fill.  Lane p reaches the end of a
 // j-tile p steps after lane 0; there it parks its 28 partial sums in LDS
-// and starts from zero, and once the last lane of the chain has done so all
-// lanes fold them into their two-sums together.
+// and starts from zero, and whenever 16 lanes have done so the wave adds them
+// to their float64 rows, a lane taking one i.
 //
 // What bounds it: VALU issue, at a clock that follows the power (2.08 GHz
 // measured).  Seven DPP moves and four v_rsq a step issue at less than the
@@ -34,8 +34,8 @@
 // SIMD; the sums over tiles live in memory as float64, which costs one
 // read-add-write of 28 values a lane and tile.  The step is 181 VALU
 // instructions for 8 interactions, 22.6 against the general kernel's 34.8.
-// Measured, general kernel to this: 2^20 bodies 652 to 514 ms, 2^18 41.8 to
-// 31 ms, 40000 1.20 to 1.02 ms; force only, 2^17 7.3 to 5.3 ms.
+// Measured, general kernel to this: 2^20 bodies 652 to 499 ms, 2^18 41.8 to
+// 31 ms, 40000 1.20 to 1.02 ms; force only, 2^17 7.3 to 5.0 ms.
 //
 // Work.  The set is cut into nb blocks of lb particles (the last one padded)
 // that stand in a ring.  Block A meets itself (one-sided, the self pair
@@ -81,6 +81,7 @@ __device__ __forceinline__ int sym_end(const SymArgs& a, int A) {
 // Quantities in the order ax ay az pot jx jy jz.
 template <int TJ, int KIND>
 __global__ __launch_bounds__(256, 4) void sym_kernel(SymArgs a) {
+    static_assert(TJ == 64 || TJ == 256, "chains of 16 or 64 lanes");
     constexpr int ROW = TJ / 4;
     constexpr int ROWS = 64 / ROW;
     constexpr int PH = ROW == 16 ? 32 : 64;         // steps between two barriers
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(256, 4) void sym_kernel(SymArgs a) {
     float eps2;   // in a VGPR: an SGPR operand halves the issue rate
     asm volatile("v_mov_b32 %0, %1" : "=v"(eps2) : "s"(a.eps2));
     // lanes at the end of a chain
-    constexpr uint64_t kLast = ROW == 16 ? 0x8000800080008000ull : ROW == 32 ? 0x8000000080000000ull : 1ull << 63;
+    constexpr uint64_t kLast = ROW == 16 ? 0x8000800080008000ull : 1ull << 63;
 
     // staging of one PH-record chunk by the first 3 PH threads
     const int sr = tid / 3, sc = tid - 3 * sr;
