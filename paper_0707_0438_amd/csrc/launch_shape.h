@@ -148,7 +148,7 @@ inline SymShape sym_shape(int64_t n, int tj, int quantities) {
         for (int r = 1; r <= 8; ++r) {
             // about r rounds of work-groups
             const int np = std::max(1, r * kSymResident / s.nb);
-            if (np == last_np) continue;
+            if (np == last_np || (np > 1 && row * (np + 1) > kSymBytes)) continue;
             last_np = np;
             const int64_t most = std::max<int64_t>(1, kSymBytes / row - np);
             const int bands = (int)((s.dists + most - 1) / most);

@@ -26,7 +26,7 @@ int main() {
                 const long long row = 8LL * q * nb::sym_stride(n);
                 if (nb::sym_stride(n) < n || nb::sym_stride(n) % 4) fail(n, "stride");
                 if ((long long)s.bytes != row * (s.nd + s.np)) fail(n, "bytes");
-                if ((long long)s.bytes > nb::kSymBytes && s.nd > 1) fail(n, "limit");
+                if ((long long)s.bytes > nb::kSymBytes) fail(n, "limit");
                 if (2 * ring + s.lp > 2147483647LL || (long long)s.np * s.nb > 2147483647LL) fail(n, "int32 range");
                 if (s.nb > 4096) continue;
                 // every unordered pair of blocks once, over all bands
