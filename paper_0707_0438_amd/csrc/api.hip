@@ -637,14 +637,8 @@ static int need_device(nbody_ctx* c) {
 static size_t reserve_part_bytes(nbody_ctx* c, int64_t max_i, int64_t max_j) {
     const int64_t ni = std::max<int64_t>(max_i, 1), nj = std::max<int64_t>(max_j, 1);
     size_t part = 0;
-    // pair-symmetric rows of every self-gravitating set up to the smaller
-    // count; beyond 2^18 particles they may fill their limit
-    const int64_t ns = std::min(std::min(ni, nj), kSymMax);
-    if (ns >= kSymMin && !c->have_override[1]) {
-        for (int64_t n = kSymMin; n < std::min<int64_t>(ns + kSymGroup, 1 << 18); n += kSymGroup)
-            part = std::max(part, sym_shape(std::min(n, ns), default_tile(1, n, n).tile_j, 7).bytes);
-        if (ns >= (1 << 18)) part = std::max(part, (size_t)kSymBytes);
-    }
+    // pair-symmetric rows of every self-gravitating set up to the smaller count
+    if (!c->have_override[1]) part = sym_bytes_upto(std::min(ni, nj));
     for (int prec = 0; prec < 2; ++prec) {
         int64_t n = ni;
         for (;;) {

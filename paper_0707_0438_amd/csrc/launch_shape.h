@@ -172,5 +172,19 @@ inline SymShape sym_shape(int64_t n, int tj, int quantities) {
     }
     return best;
 }
+// Bytes of the rows of every pair-symmetric evaluation of up to `most`
+// particles, of either kind.  A shape depends on n by its group of kSymGroup
+// and by the j-tile, which changes once over all sizes, so each group's first
+// and last size stand for it.  From 2^18 on: all that a launch may take.
+inline size_t sym_bytes_upto(int64_t most) {
+    if (most < kSymMin) return 0;
+    if (most >= (1 << 18)) return (size_t)kSymBytes;
+    size_t bytes = 0;
+    for (int64_t first = kSymMin; first <= most; first = sym_stride(first) + 1)
+        for (const int64_t n : {first, std::min(sym_stride(first), most)})
+            for (int kind = 0; kind < 2; ++kind)
+                bytes = std::max(bytes, sym_shape(n, default_tile_kind(kind, 1, n, n).tile_j, kind == 1 ? 4 : 7).bytes);
+    return bytes;
+}
 
 }  // namespace nb

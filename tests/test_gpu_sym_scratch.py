@@ -1,0 +1,40 @@
+"""GPU: scratch of the pair-symmetric evaluation.  NBODY_DEBUG_FAIL_ALLOC=k
+fails the k-th device allocation of a context from the host; where the rows
+cannot be had the general kernel runs, whose sums over tiles are formed in
+another order, so the bits tell which of the two ran."""
+import pytest
+
+import nbody_inputs as ics
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+EPS = 1e-3
+
+
+def _set(n):
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    p = ics.plummer(n, 31, "salpeter")
+    return dev(p.pos), dev(p.vel), dev(p.mass), torch.arange(n, dtype=torch.int32, device="cuda")
+
+
+def _equal(a, b):
+    import torch
+    return all(torch.equal(u, w) for u, w in zip(a, b))
+
+
+@pytest.mark.parametrize("n", [25000, 65535])
+def test_reserved_set_allocates_nothing(n, monkeypatch):
+    """After nbody_reserve(n, n), with its four allocations (i records, j
+    records, rows, flag), no evaluation of n bodies allocates."""
+    import paper_0707_0438_amd as nb
+    x, v, m, own = _set(n)
+    with nb.Context(0) as c:
+        ref = c.force(x, v, x, v, m, EPS, i_self=own)
+        refa = c.force_acc(x, x, m, EPS, i_self=own)
+    monkeypatch.setenv("NBODY_DEBUG_FAIL_ALLOC", "5")
+    with nb.Context(0) as c:
+        c.reserve(n, n)
+        assert _equal(c.force(x, v, x, v, m, EPS, i_self=own), ref)
+        assert _equal(c.force_acc(x, x, m, EPS, i_self=own), refa)
