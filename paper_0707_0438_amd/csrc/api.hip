@@ -230,14 +230,19 @@ static bool valid_tile(const nbody_tile& t) {
            force_variant_exists(1, t.ipt, t.tile_j, t.wg, t.jsrc, t.unroll, t.waves, false);
 }
 
-static nbody_tile pick_tile(nbody_ctx* c, int prec, int64_t ni, int64_t nj) {
+// Launch shape of an evaluation kind; split 0 where choose_split is to fill
+// it in.  Tuned entries hold full evaluations' (kind 0) shapes only.
+static nbody_tile base_tile(nbody_ctx* c, int kind, int prec, int64_t ni, int64_t nj) {
     nbody_tile t;
-    if (c->have_override[prec]) {
-        t = c->override_tile[prec];
-    } else if (!c->tune.lookup(prec, ni, nj, &t)) {
-        t = default_tile(prec, ni, nj);
-    }
-    if (t.split <= 0) t.split = choose_split(prec, ni, nj, t);
+    if (c->have_override[prec]) return c->override_tile[prec];
+    if (kind == 0 && c->tune.lookup(prec, ni, nj, &t)) return t;
+    return default_tile_kind(kind, prec, ni, nj);
+}
+
+static nbody_tile pick_tile(nbody_ctx* c, int prec, int64_t ni, int64_t nj, int kind = 0) {
+    nbody_tile t = base_tile(c, kind, prec, ni, nj);
+    // (a pinned shape's ranges are the full evaluation's for every kind)
+    if (t.split <= 0) t.split = choose_split(prec, ni, nj, t, c->have_override[prec] ? 0 : kind);
     return t;
 }
 
@@ -271,10 +276,8 @@ static int run_force(nbody_ctx* c, hipStream_t st, int prec, double G, double ep
     nbody_tile t;
     if (forced) {
         t = *forced;
-    } else if (kind == 0 || c->have_override[prec]) {
-        t = pick_tile(c, prec, ni, nj);   // tuned entries hold kind-0 shapes only
     } else {
-        t = default_tile_kind(kind, prec, ni, nj);
+        t = pick_tile(c, prec, ni, nj, kind);
     }
     if (t.split <= 0) t.split = choose_split(prec, ni, nj, t, kind);
     const bool eps0 = eps == 0.0;
@@ -410,9 +413,7 @@ static int sym_tile(nbody_ctx* c, int prec, double eps, int64_t n, int kind) {
 
 // Split-partial bytes of the general kernel for a direct call (eps > 0).
 static size_t direct_part_bytes(nbody_ctx* c, int prec, int64_t ni, int64_t nj, int kind) {
-    nbody_tile t = kind == 0 || c->have_override[prec] ? pick_tile(c, prec, ni, nj)
-                                                       : default_tile_kind(kind, prec, ni, nj);
-    if (t.split <= 0) t.split = choose_split(prec, ni, nj, t, kind);
+    const nbody_tile t = pick_tile(c, prec, ni, nj, kind);
     int nb, S, jc;
     split_plan(ni, nj, t.wg * t.ipt, t.tile_j, t.split, &nb, &S, &jc);
     return S > 1 ? sizeof(float2) * 8 * (size_t)S * (size_t)ni : 0;
@@ -630,28 +631,19 @@ static int need_device(nbody_ctx* c) {
     return NBODY_OK;
 }
 
-// Split-partial bytes of the shapes the next calls would take for up to
-// max_i i-particles against max_j j: evaluated at max_i and at every power
-// of two below it (the long-evaluation rule keeps S x n_i about constant, so
-// the largest is near one of these).  Host arithmetic only.
+// Split-partial and pair-symmetric bytes of the next calls, of every kind, for
+// up to max_i i-particles against up to max_j j.  Host arithmetic only.
 static size_t reserve_part_bytes(nbody_ctx* c, int64_t max_i, int64_t max_j) {
     const int64_t ni = std::max<int64_t>(max_i, 1), nj = std::max<int64_t>(max_j, 1);
     size_t part = 0;
     // pair-symmetric rows of every self-gravitating set up to the smaller count
     if (!c->have_override[1]) part = sym_bytes_upto(std::min(ni, nj));
-    for (int prec = 0; prec < 2; ++prec) {
-        int64_t n = ni;
-        for (;;) {
-            const nbody_tile t = pick_tile(c, prec, n, nj);
-            int nb, S, jc;
-            split_plan(n, nj, t.wg * t.ipt, t.tile_j, t.split, &nb, &S, &jc);
-            if (S > 1) part = std::max(part, sizeof(float2) * 8 * (size_t)S * (size_t)n);
-            if (n <= 1) break;
-            // the largest power of two below n (n strictly decreases)
-            const int64_t p2 = (int64_t)1 << (63 - __builtin_clzll((unsigned long long)n));
-            n = p2 < n ? p2 : n / 2;
+    for (int kind = 0; kind < 3; ++kind)
+        for (int prec = 0; prec < 2; ++prec) {
+            const int64_t rows = part_rows_upto(
+                prec, ni, nj, [&](int64_t n, int64_t m) { return base_tile(c, kind, prec, n, m); });
+            part = std::max(part, sizeof(float2) * 8 * (size_t)rows);
         }
-    }
     return part;
 }
 

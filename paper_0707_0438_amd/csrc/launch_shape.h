@@ -118,6 +118,51 @@ inline nbody_tile default_tile_kind(int kind, int prec, int64_t ni, int64_t nj) 
     return default_tile(prec, ni, nj, kind == 0);
 }
 
+// No fewer than choose_split gives for this shape against nj j or fewer, of
+// any kind: its rules without the rounding to whole tiles, which can leave a
+// larger j set with fewer ranges than a smaller one.
+inline int64_t split_bound(int prec, int64_t ni, int64_t nj, const nbody_tile& t) {
+    const int64_t per = (int64_t)t.wg * t.ipt, nb = std::max<int64_t>(1, (ni + per - 1) / per);
+    int64_t S = nb < 1024 ? std::min((2048 + nb - 1) / nb, nj / t.tile_j) : 1;
+    if (prec == 1 && t.tile_j == 64) S = std::max(S, std::min((4096 + nb - 1) / nb, nj / (5 * t.tile_j)));
+    const int64_t Sl = std::min((kLongWG + nb - 1) / nb, nj / (kLongTiles * t.tile_j));
+    return std::max(S, std::min(Sl, kLongPartBytes / (64 * std::max<int64_t>(ni, 1))));
+}
+
+// The most split-partial rows (j-ranges x i) that any evaluation of up to
+// max_i i-particles against up to max_j j-particles takes; tile_of(n_i, n_j)
+// is its launch shape, split 0 where choose_split fills it in.  The ranges
+// fall in steps as the i-blocks grow, towards one of three work-group counts,
+// so the most rows stand just before a step; and the j counts at which the
+// default shape changes may take more ranges than max_j itself.
+template <class TileOf>
+int64_t part_rows_upto(int prec, int64_t max_i, int64_t max_j, TileOf tile_of) {
+    int64_t rows = 0;
+    auto at = [&](int64_t n) {
+        if (n < 1 || n > max_i) return;
+        for (const int64_t j : {max_j, (((int64_t)1 << 32) - 1) / n, (int64_t)2048, (int64_t)512, n}) {
+            const int64_t m = std::min(j, max_j);
+            if (m < 1) continue;
+            const nbody_tile t = tile_of(n, m);
+            const int tj = std::min(t.tile_j, 64);   // eps = 0 and the other kinds may go back to 64 or 128
+            const int64_t S = t.split > 0 ? std::min<int64_t>(t.split, (m + tj - 1) / tj) : split_bound(prec, n, m, t);
+            if (S > 1) rows = std::max(rows, S * n);
+        }
+    };
+    at(max_i);
+    for (const int64_t j : {max_j, (int64_t)2048, (int64_t)512})   // last size below the large shape
+        if (j > 0) at((((int64_t)1 << 32) - 1) / j);
+    at(65535);                                                    // that of a set against itself
+    for (int64_t n = 1; n < max_i; n *= 2) at(n), at(n - 1);      // tuned shapes go by powers of two
+    for (const int64_t per : {64, 128, 256, 512, 1024})
+        for (const int64_t groups : {(int64_t)2048, (int64_t)4096, kLongWG})
+            for (int64_t k = 1; (k - 1) * (k - 1) <= groups; ++k) {
+                at(k * per);
+                if (k > 1) at(((groups + k - 2) / (k - 1) - 1) * per);   // the most blocks with k ranges
+            }
+    return rows;
+}
+
 // Shape of the pair-symmetric evaluation of n particles (sym.hip): blocks of
 // lb particles, bands of nd block distances, each block's stretch of a band
 // in np pieces of lp.  tj: the j-tile whose partial sums it forms (64 or 256).
