@@ -26,9 +26,16 @@ constexpr int64_t kMaxN = 2147483647LL;
 // The differentiable run's elementwise kernels index [3][n] rows as one int32 range.
 constexpr int64_t kMaxShared = kMaxN / 3;
 
+// Device memory that goes with its owner (whose device is current then).
 struct DevBuf {
     void* p = nullptr;
     size_t bytes = 0;
+    DevBuf() = default;
+    DevBuf(const DevBuf&) = delete;
+    DevBuf& operator=(const DevBuf&) = delete;
+    ~DevBuf() {
+        if (p) (void)hipFree(p);
+    }
 };
 
 // Caller-provided room for the split partial sums (the allocation-free
@@ -604,8 +611,8 @@ int nbody_create(nbody_ctx** ctx, int device, const char* tune_cache_path) {
 
 int nbody_destroy(nbody_ctx* c) {
     if (!c) return NBODY_OK;
+    DeviceGuard g(c->device);
     if (c->device >= 0) {
-        DeviceGuard g(c->device);
         for (hipEvent_t x : c->ev) (void)hipEventDestroy(x);
         if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
         if (c->graph) (void)hipGraphDestroy(c->graph);
@@ -613,11 +620,6 @@ int nbody_destroy(nbody_ctx* c) {
             if (x) (void)hipEventDestroy(x);
         if (c->gstream) (void)hipStreamDestroy(c->gstream);
         if (c->trace) fclose(c->trace);
-        DevBuf* bufs[] = {&c->ipack, &c->jpack, &c->part, &c->sel, &c->scratch64,
-                          &c->vrec_i, &c->vrec_j, &c->vpart, &c->integ, &c->hist, &c->bplan,
-                          &c->bstate, &c->lf};
-        for (DevBuf* b : bufs)
-            if (b->p) (void)hipFree(b->p);
     }
     delete c;
     return NBODY_OK;

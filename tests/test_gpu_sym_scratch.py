@@ -38,3 +38,27 @@ def test_reserved_set_allocates_nothing(n, monkeypatch):
         c.reserve(n, n)
         assert _equal(c.force(x, v, x, v, m, EPS, i_self=own), ref)
         assert _equal(c.force_acc(x, x, m, EPS, i_self=own), refa)
+
+
+def test_destroy_returns_every_allocation():
+    """2000 contexts that each made the flag of the identity check (nbody_reserve
+    of a set that size): the smallest device allocation is 4 KiB, so one kept
+    by each would take 8 MiB of the free memory; 4 MiB are allowed for what
+    the runtime keeps."""
+    import torch
+    import paper_0707_0438_amd as nb
+
+    def once():
+        with nb.Context(0) as c:
+            for prec in ("ds", "fp32"):   # no rows, no partials: the flag and the records alone
+                c.set_tile(prec, 64, 1, 128, split=1)
+            c.reserve(24576, 24576)
+
+    for _ in range(50):
+        once()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info(0)[0]
+    for _ in range(2000):
+        once()
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info(0)[0] < 4 << 20
