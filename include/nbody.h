@@ -124,7 +124,8 @@ typedef struct {
  *    0), as nbody_set_tile does, for each precision that has the shape
  *    compiled; NBODY_ERR_ARG from nbody_create when no precision has it.
  *  NBODY_DEBUG_FAIL_ALLOC=<k>  the k-th device allocation of the context
- *    fails with NBODY_ERR_NOMEM (failure-path testing).
+ *    fails with NBODY_ERR_NOMEM (failure-path testing); one that the call
+ *    can do without (see nbody_force) fails and the call goes on.
  *  NBODY_DEBUG_SELF_CHECK=1  see nbody_force. */
 int nbody_create(nbody_ctx **ctx, int device, const char *tune_cache_path);
 
@@ -193,8 +194,8 @@ int nbody_autotune(nbody_ctx *ctx, hipStream_t stream, nbody_prec prec, double G
  * evaluated pair by pair, each pair serving both of its particles: the same
  * float32 partial sums, added up in another order (differences of order
  * 1e-14), with at most 2 GiB of scratch; where that cannot be had, the
- * general kernel runs.  An i_self value outside
- * [0, n_j) excludes nothing.  With the environment variable
+ * general kernel runs, and does so from then on for sets of that size or
+ * more in this context.  An i_self value outside [0, n_j) excludes nothing.  With the environment variable
  * NBODY_DEBUG_SELF_CHECK=1 set when the context is created, the call also
  * checks that each i row equals the j row i_self names (the same particle)
  * and that every i_self < n_j, synchronising the stream, and returns

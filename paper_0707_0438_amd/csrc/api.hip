@@ -16,6 +16,7 @@
 #include "nbody.h"
 #include "force_block.h"
 #include "nbody_internal.h"
+#include "scratch.h"
 #include "tune.h"
 
 using namespace nb;
@@ -25,18 +26,6 @@ namespace {
 constexpr int64_t kMaxN = 2147483647LL;
 // The differentiable run's elementwise kernels index [3][n] rows as one int32 range.
 constexpr int64_t kMaxShared = kMaxN / 3;
-
-// Device memory that goes with its owner (whose device is current then).
-struct DevBuf {
-    void* p = nullptr;
-    size_t bytes = 0;
-    DevBuf() = default;
-    DevBuf(const DevBuf&) = delete;
-    DevBuf& operator=(const DevBuf&) = delete;
-    ~DevBuf() {
-        if (p) (void)hipFree(p);
-    }
-};
 
 // Caller-provided room for the split partial sums (the allocation-free
 // entry point): run_force takes its partials from here, never allocates,
@@ -101,6 +90,9 @@ struct nbody_ctx {
     bool have_override[2] = {false, false};
     nbody_tile override_tile[2];
     nb::TuneCache tune;
+    // pair-symmetric rows: sets that need this many bytes or more take the
+    // general kernel (an allocation of that size has failed)
+    size_t sym_denied = SIZE_MAX;
     int32_t sym_epoch = 0;    // calls that had i_self checked for the identity
     bool symflag_clear = false;   // symflag holds an epoch (0 at first), not what its memory held before
     int alloc_count = 0;
@@ -206,6 +198,19 @@ static int dev_alloc(nbody_ctx* c, DevBuf& b, size_t bytes) {
     b.p = p;
     b.bytes = bytes;
     return NBODY_OK;
+}
+
+// The same for memory that a call can do without: false, with no error set and
+// b as it was, when there is none.
+static bool dev_try_alloc(nbody_ctx* c, DevBuf& b, size_t bytes) {
+    return grow_or_keep(b, bytes, [c](size_t n) -> void* {
+        ++c->alloc_count;
+        if (c->fail_alloc_at > 0 && c->alloc_count == c->fail_alloc_at) return nullptr;
+        void* p = nullptr;
+        if (hipMalloc(&p, n) == hipSuccess) return p;
+        (void)hipGetLastError();
+        return nullptr;
+    });
 }
 
 static bool aligned8(const void* p) { return ((uintptr_t)p & 7u) == 0; }
@@ -437,8 +442,12 @@ static int run_sym(nbody_ctx* c, hipStream_t st, int tj, int kind, double G, dou
     // (with the check, room for the general kernel's partials too: it is
     // launched behind, into the same buffer)
     const size_t need = std::max(s.bytes, check ? direct_part_bytes(c, 1, n, n, kind) : 0);
-    if (dev_alloc(c, c->part, need) != NBODY_OK) {
-        c->err.clear();
+    if (need >= c->sym_denied) return NBODY_OK;
+    if (!dev_try_alloc(c, c->part, need)) {
+        // not asked for again: a failing allocation in every step of a run
+        // would cost more than the pairs saved, and a run whose kernel changes
+        // on the way would not repeat bit for bit
+        c->sym_denied = need;
         return NBODY_OK;
     }
     *done = true;
@@ -519,10 +528,7 @@ static int force_rows(nbody_ctx* c, hipStream_t st, int p, double G, double eps,
                       int32_t* nn, double* nn_r2) {
     const bool own = n_i == n_j && same_src(I, J);
     int tj = own && i_self ? sym_tile(c, p, eps, n_i, kind) : 0;
-    if (tj && dev_alloc(c, c->symflag, 256) != NBODY_OK) {
-        c->err.clear();
-        tj = 0;
-    }
+    if (tj && !dev_try_alloc(c, c->symflag, 256)) tj = 0;
     if (tj) {
         if (!c->symflag_clear) {
             const hipError_t e = launch_fill_i32((int*)c->symflag.p, 64, 0, st);

@@ -62,3 +62,28 @@ def test_destroy_returns_every_allocation():
         once()
     torch.cuda.synchronize()
     assert before - torch.cuda.mem_get_info(0)[0] < 4 << 20
+
+
+def test_rows_that_cannot_be_had_are_not_asked_for_again(monkeypatch):
+    """The rows' allocation (the third: flag, records, rows) fails: this call
+    and the later ones of that size take the general kernel, and the error
+    text of an earlier call stays."""
+    import paper_0707_0438_amd as nb
+    n = 25000
+    x, v, m, own = _set(n)
+    with nb.Context(0) as g:
+        sym = g.force(x, v, x, v, m, EPS, i_self=own)
+        t = g.get_tile(n, n)
+        t["split"] = 0
+        g.set_tile("ds", **t)
+        ref = g.force(x, v, x, v, m, EPS, i_self=own)
+        assert not _equal(sym, ref)
+    monkeypatch.setenv("NBODY_DEBUG_FAIL_ALLOC", "3")
+    with nb.Context(0) as c:
+        with pytest.raises(nb.NBodyError):
+            c.force(x, v, x, v, m, -1.0, i_self=own)
+        text = c.last_error()
+        assert text
+        for _ in range(3):
+            assert _equal(c.force(x, v, x, v, m, EPS, i_self=own), ref)
+        assert c.last_error() == text
