@@ -132,7 +132,11 @@ int nbody_create(nbody_ctx **ctx, int device, const char *tune_cache_path);
 /* Release the context and all of its device memory.  NULL is accepted. */
 int nbody_destroy(nbody_ctx *ctx);
 
-/* Pre-size scratch for up to max_i i-particles against max_j j-particles. */
+/* Pre-size scratch for evaluations of up to max_i i-particles against up to
+ * max_j j-particles, which then allocate nothing.  Where the rows of the
+ * pair-symmetric evaluation (see nbody_force; up to 2 GiB) cannot be had, the
+ * sets that need them take the general kernel from then on; the call still
+ * succeeds. */
 int nbody_reserve(nbody_ctx *ctx, int64_t max_i, int64_t max_j);
 
 /* Wait for all work on `stream`; reports deferred device errors. */
@@ -194,12 +198,12 @@ int nbody_autotune(nbody_ctx *ctx, hipStream_t stream, nbody_prec prec, double G
  * evaluated pair by pair, each pair serving both of its particles: the same
  * float32 partial sums, added up in another order (differences of order
  * 1e-14), with at most 2 GiB of scratch; where that cannot be had, the
- * general kernel runs, and does so from then on for sets of that size or
- * more in this context.  An i_self value outside [0, n_j) excludes nothing.  With the environment variable
- * NBODY_DEBUG_SELF_CHECK=1 set when the context is created, the call also
- * checks that each i row equals the j row i_self names (the same particle)
- * and that every i_self < n_j, synchronising the stream, and returns
- * NBODY_ERR_ARG when one does not.
+ * general kernel runs, and does so for sets of that size or more until the
+ * context's next nbody_reserve.  An i_self value outside [0, n_j) excludes
+ * nothing.  With the environment variable NBODY_DEBUG_SELF_CHECK=1 set when
+ * the context is created, the call also checks that each i row equals the j
+ * row i_self names (the same particle) and that every i_self < n_j,
+ * synchronising the stream, and returns NBODY_ERR_ARG when one does not.
  * I.m is unused.  Returns NBODY_ERR_ARG for NULL rows, n_i < 0, n_j < 0,
  * counts above 2^31 - 1, non-finite G or eps, eps < 0. */
 int nbody_force(nbody_ctx *ctx, hipStream_t stream, nbody_prec prec, double G, double eps,

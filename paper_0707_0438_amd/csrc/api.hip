@@ -431,6 +431,12 @@ static size_t direct_part_bytes(nbody_ctx* c, int prec, int64_t ni, int64_t nj, 
     return S > 1 ? sizeof(float2) * 8 * (size_t)S * (size_t)ni : 0;
 }
 
+// Bytes that run_sym works in.  With the check, room for the general kernel's
+// partials too: it is launched behind, into the same buffer.
+static size_t sym_need(nbody_ctx* c, const SymShape& s, int kind, int64_t n, bool check) {
+    return std::max(s.bytes, check ? direct_part_bytes(c, 1, n, n, kind) : 0);
+}
+
 // Pair-symmetric evaluation of the n packed records; *done = false when its
 // rows do not fit in memory (the caller then takes the general kernel).
 // check: only if the pack pass found i_self to be the identity.
@@ -439,9 +445,7 @@ static int run_sym(nbody_ctx* c, hipStream_t st, int tj, int kind, double G, dou
     const int nq = kind == 1 ? 4 : 7;
     const SymShape s = sym_shape(n, tj, nq);
     *done = false;
-    // (with the check, room for the general kernel's partials too: it is
-    // launched behind, into the same buffer)
-    const size_t need = std::max(s.bytes, check ? direct_part_bytes(c, 1, n, n, kind) : 0);
+    const size_t need = sym_need(c, s, kind, n, check);
     if (need >= c->sym_denied) return NBODY_OK;
     if (!dev_try_alloc(c, c->part, need)) {
         // not asked for again: a failing allocation in every step of a run
@@ -528,6 +532,9 @@ static int force_rows(nbody_ctx* c, hipStream_t st, int p, double G, double eps,
                       int32_t* nn, double* nn_r2) {
     const bool own = n_i == n_j && same_src(I, J);
     int tj = own && i_self ? sym_tile(c, p, eps, n_i, kind) : 0;
+    if (tj && c->sym_denied != SIZE_MAX &&
+        sym_need(c, sym_shape(n_i, tj, kind == 1 ? 4 : 7), kind, n_i, true) >= c->sym_denied)
+        tj = 0;
     if (tj && !dev_try_alloc(c, c->symflag, 256)) tj = 0;
     if (tj) {
         if (!c->symflag_clear) {
@@ -639,13 +646,11 @@ static int need_device(nbody_ctx* c) {
     return NBODY_OK;
 }
 
-// Split-partial and pair-symmetric bytes of the next calls, of every kind, for
-// up to max_i i-particles against up to max_j j.  Host arithmetic only.
+// Split-partial bytes of the next calls, of every kind, for up to max_i
+// i-particles against up to max_j j.  Host arithmetic only.
 static size_t reserve_part_bytes(nbody_ctx* c, int64_t max_i, int64_t max_j) {
     const int64_t ni = std::max<int64_t>(max_i, 1), nj = std::max<int64_t>(max_j, 1);
     size_t part = 0;
-    // pair-symmetric rows of every self-gravitating set up to the smaller count
-    if (!c->have_override[1]) part = sym_bytes_upto(std::min(ni, nj));
     for (int kind = 0; kind < 3; ++kind)
         for (int prec = 0; prec < 2; ++prec) {
             const int64_t rows = part_rows_upto(
@@ -665,9 +670,19 @@ int nbody_reserve(nbody_ctx* c, int64_t max_i, int64_t max_j) {
     const size_t ni = (size_t)std::max<int64_t>(max_i, 1), nj = (size_t)std::max<int64_t>(max_j, 1);
     int rc = dev_alloc(c, c->ipack, sizeof(float4) * kRecDS * ni);
     if (!rc) rc = dev_alloc(c, c->jpack, sizeof(float4) * kRecDS * nj);
-    if (!rc && part > 0) rc = dev_alloc(c, c->part, part);
-    if (!rc && std::min(max_i, max_j) >= kSymMin) rc = dev_alloc(c, c->symflag, 256);
-    return rc;
+    if (rc) return rc;
+    // pair-symmetric rows of every self-gravitating set up to the smaller
+    // count; without them such a set takes the general kernel
+    const size_t sym = c->have_override[1] ? 0 : sym_bytes_upto(std::min(max_i, max_j));
+    if (sym > 0) {
+        c->sym_denied = SIZE_MAX;
+        if (!dev_try_alloc(c, c->symflag, 256) || !dev_try_alloc(c, c->part, std::max(part, sym))) {
+            if ((rc = dev_alloc(c, c->part, part))) return rc;
+            c->sym_denied = c->part.bytes + 1;   // the calls it covers allocate nothing
+        }
+        return NBODY_OK;
+    }
+    return dev_alloc(c, c->part, part);
 }
 
 int nbody_sync(nbody_ctx* c, hipStream_t st) {

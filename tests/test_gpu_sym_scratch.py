@@ -87,3 +87,25 @@ def test_rows_that_cannot_be_had_are_not_asked_for_again(monkeypatch):
         for _ in range(3):
             assert _equal(c.force(x, v, x, v, m, EPS, i_self=own), ref)
         assert c.last_error() == text
+
+
+@pytest.mark.parametrize("k", [3, 4])
+def test_reserve_without_room_for_the_rows(k, monkeypatch):
+    """nbody_reserve whose flag or rows (its third and fourth allocation)
+    cannot be had succeeds, and the set takes the general kernel; reserved
+    again, with room, it is evaluated pair by pair."""
+    import paper_0707_0438_amd as nb
+    n = 25000
+    x, v, m, own = _set(n)
+    with nb.Context(0) as g:
+        sym = g.force(x, v, x, v, m, EPS, i_self=own)
+        t = g.get_tile(n, n)
+        t["split"] = 0
+        g.set_tile("ds", **t)
+        ref = g.force(x, v, x, v, m, EPS, i_self=own)
+    monkeypatch.setenv("NBODY_DEBUG_FAIL_ALLOC", str(k))
+    with nb.Context(0) as c:
+        c.reserve(n, n)
+        assert _equal(c.force(x, v, x, v, m, EPS, i_self=own), ref)
+        c.reserve(n, n)
+        assert _equal(c.force(x, v, x, v, m, EPS, i_self=own), sym)
