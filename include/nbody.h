@@ -153,8 +153,9 @@ int nbody_abi_version(void);
  * launch stream.  nbody_kernel_time waits for the recorded events, returns
  * the summed kernel time in milliseconds and the number of launches (HOST
  * outputs) and starts a new tally.  An evaluation in several launches (the
- * pair-symmetric one of a large set) counts as one.  The events stay owned
- * by the context. */
+ * pair-symmetric one of a large set, and the general kernel behind it, which
+ * leaves at once unless i_self is not the identity) counts as one, with the
+ * time of them all.  The events stay owned by the context. */
 int nbody_kernel_timing(nbody_ctx *ctx, int enable);
 int nbody_kernel_time(nbody_ctx *ctx, double *total_ms, int64_t *launches);
 

@@ -103,8 +103,9 @@ struct nbody_ctx {
     FILE* trace = nullptr;
     // kernel timing: event pairs recorded around each pairwise-kernel launch
     bool timing = false;
-    std::vector<hipEvent_t> ev;   // 2 per launch
+    std::vector<hipEvent_t> ev;   // 2 per launch, or bands of launches
     size_t ev_used = 0;
+    int64_t ev_launches = 0;      // evaluations that they are of
 };
 
 struct nbody_hermite {
@@ -259,8 +260,8 @@ static nbody_tile pick_tile(nbody_ctx* c, int prec, int64_t ni, int64_t nj, int 
 }
 
 // Kernel timing: record the event before a pairwise launch; *end is the one
-// to record after it.
-static int timing_begin(nbody_ctx* c, hipStream_t st, hipEvent_t* end) {
+// to record after it.  again: a further launch of the evaluation counted last.
+static int timing_begin(nbody_ctx* c, hipStream_t st, hipEvent_t* end, bool again = false) {
     while (c->ev.size() < c->ev_used + 2) {
         hipEvent_t x;
         if (hipEventCreate(&x) != hipSuccess) return set_err(c, NBODY_ERR_DEVICE, "event create");
@@ -269,6 +270,7 @@ static int timing_begin(nbody_ctx* c, hipStream_t st, hipEvent_t* end) {
     const hipEvent_t begin = c->ev[c->ev_used];
     *end = c->ev[c->ev_used + 1];
     c->ev_used += 2;
+    if (!again) ++c->ev_launches;
     if (hipEventRecord(begin, st) != hipSuccess) return set_err(c, NBODY_ERR_DEVICE, "event record");
     return NBODY_OK;
 }
@@ -353,8 +355,8 @@ static int run_force(nbody_ctx* c, hipStream_t st, int prec, double G, double ep
         if (kind == 2) a.nnpart = a.part + 7 * (size_t)S * (size_t)ni;
     }
     hipEvent_t te = nullptr;
-    if (c->timing && !fixed && !only)
-        if (int rc = timing_begin(c, st, &te)) return rc;
+    if (c->timing && !fixed)
+        if (int rc = timing_begin(c, st, &te, only != nullptr)) return rc;
     hipError_t e = launch_force(prec, ipt, tj, wg, jsrc, unr, wpe, eps0, nb, S, a, st, kind);
     if (e != hipSuccess) return hip_err(c, e, "force kernel launch");
     if (te && hipEventRecord(te, st) != hipSuccess) return set_err(c, NBODY_ERR_DEVICE, "event record");
@@ -700,6 +702,7 @@ int nbody_kernel_timing(nbody_ctx* c, int enable) {
     if (int rc = need_device(c)) return rc;
     c->timing = enable == 1;
     c->ev_used = 0;
+    c->ev_launches = 0;
     return NBODY_OK;
 }
 
@@ -717,8 +720,9 @@ int nbody_kernel_time(nbody_ctx* c, double* total_ms, int64_t* launches) {
         tot += ms;
     }
     *total_ms = tot;
-    *launches = (int64_t)(c->ev_used / 2);
+    *launches = c->ev_launches;
     c->ev_used = 0;
+    c->ev_launches = 0;
     return NBODY_OK;
 }
 
