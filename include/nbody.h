@@ -174,7 +174,10 @@ int nbody_get_tile(nbody_ctx *ctx, nbody_prec prec, int64_t n_i, int64_t n_j, nb
  * and shape bucket (floor log2 of n_i and n_j), and write the cache file if
  * the context has one.  `out` receives the last evaluation.  *best and
  * *best_ms (HOST, may be NULL) report the choice and its time per
- * evaluation in milliseconds.  Synchronises `stream`. */
+ * evaluation in milliseconds.  Given one self-gravitating set as I and J, the
+ * pair-symmetric evaluation that nbody_force takes for it (see there) is
+ * timed too: nbody_force leaves it for the tuned shape where that was faster.
+ * Synchronises `stream`. */
 int nbody_autotune(nbody_ctx *ctx, hipStream_t stream, nbody_prec prec, double G, double eps,
                    int64_t n_i, nbody_src I, int64_t n_j, nbody_src J, nbody_out out, int reps,
                    nbody_tile *best, double *best_ms);
@@ -195,7 +198,8 @@ int nbody_autotune(nbody_ctx *ctx, hipStream_t stream, nbody_prec prec, double G
  * contributes nothing to a, jerk or pot and the large self potential
  * m_i/eps never enters a float32 partial sum.  A DS self-gravitating set of
  * 24576 to 2^24 particles with eps > 0 (I the same rows as J, i_self the
- * identity, which the device checks; no pinned or tuned launch shape) is
+ * identity, which the device checks; no pinned launch shape, nor a tuned one
+ * that nbody_autotune found to be faster) is
  * evaluated pair by pair, each pair serving both of its particles: the same
  * float32 partial sums, added up in another order (differences of order
  * 1e-14), with at most 2 GiB of scratch; where that cannot be had, the

@@ -411,16 +411,15 @@ static int pack_rows(nbody_ctx* c, hipStream_t st, int prec, int64_t n, const nb
 
 // Whether one self-gravitating set takes the pair-symmetric evaluation, and
 // with which fold interval (j-tile): 0 for the general kernel.  It forms the
-// partial sums of the default tiles of 64 and 256 records, so a pinned or
-// tuned launch shape keeps the general kernel, as do float32 (one float32
-// sum over all j of a range, a serial chain), eps = 0 and softenings whose
-// square leaves the normal float32 range.
-static int sym_tile(nbody_ctx* c, int prec, double eps, int64_t n, int kind) {
+// partial sums of the default tiles of 64 and 256 records, so a pinned launch
+// shape keeps the general kernel, as do a tuned one that was measured faster,
+// float32 (one float32 sum over all j of a range, a serial chain), eps = 0 and
+// softenings whose square leaves the normal float32 range.
+static int sym_tile(nbody_ctx* c, int prec, double eps, int64_t n, int kind, bool tuned = true) {
     if (prec != 1 || kind > 1 || c->have_override[prec] || n < kSymMin || n > kSymMax) return 0;
     const float e2 = (float)(eps * eps);
     if (!(e2 >= 1.17549435e-38f) || !isfinite(e2)) return 0;
-    nbody_tile t;
-    if (kind == 0 && c->tune.lookup(prec, n, n, &t)) return 0;
+    if (tuned && kind == 0 && c->tune.beats_symmetric(prec, n)) return 0;
     const int tj = default_tile_kind(kind, prec, n, n).tile_j;
     return tj == 64 || tj == 256 ? tj : 0;
 }
@@ -2348,7 +2347,8 @@ int nbody_autotune(nbody_ctx* c, hipStream_t st, nbody_prec prec, double G, doub
     int rc = pack_rows(c, st, p, n_j, J, true, c->jpack);
     if (rc) return rc;
     const float4* ip = (const float4*)c->jpack.p;
-    if (!(n_i == n_j && same_src(I, J))) {
+    const bool own = n_i == n_j && same_src(I, J);
+    if (!own) {
         rc = pack_rows(c, st, p, n_i, I, false, c->ipack);
         if (rc) return rc;
         ip = (const float4*)c->ipack.p;
@@ -2368,38 +2368,45 @@ int nbody_autotune(nbody_ctx* c, hipStream_t st, nbody_prec prec, double G, doub
             ve == (eps == 0.0))
             cand.push_back(nbody_tile{vt, vi, vw, 0, vj, vu, vo});
     }
+    // one evaluation to warm up, then the mean of `reps`
+    auto timed = [&](auto eval, double* per) {
+        if (int r = eval()) return r;
+        hipError_t e = hipEventRecord(e0, st);
+        for (int k = 0; k < reps && e == hipSuccess; ++k)
+            if (int r = eval()) return r;
+        if (e == hipSuccess) e = hipEventRecord(e1, st);
+        if (e == hipSuccess) e = hipEventSynchronize(e1);
+        float ms = 0.f;
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        if (e != hipSuccess) return hip_err(c, e, "autotune timing");
+        *per = (double)ms / reps;
+        return (int)NBODY_OK;
+    };
+    // the pair-symmetric evaluation first: `out` gets the last one
+    double sym_ms = 0.0;
+    if (const int tj = own ? sym_tile(c, p, eps, n_i, 0, false) : 0) {
+        bool done = false;
+        rc = timed([&] { return run_sym(c, st, tj, 0, G, eps, n_i, ip, o, false, &done); }, &sym_ms);
+        if (!done) sym_ms = 0.0;
+    }
     nbody_tile bt{};
     double bms = 1e300;
     for (size_t ci = 0; ci < cand.size() && !rc; ++ci) {
-            {
-                nbody_tile t = cand[ci];
-
-                t.split = choose_split(p, n_i, n_j, t);
-                rc = run_force(c, st, p, G, eps, n_i, ip, nullptr, nullptr, 0, n_j, (const float4*)c->jpack.p, o, &t);
-                if (rc) break;
-                hipError_t e = hipEventRecord(e0, st);
-                for (int r = 0; r < reps && e == hipSuccess && !rc; ++r)
-                    rc = run_force(c, st, p, G, eps, n_i, ip, nullptr, nullptr, 0, n_j, (const float4*)c->jpack.p, o, &t);
-                if (rc) break;
-                if (e == hipSuccess) e = hipEventRecord(e1, st);
-                if (e == hipSuccess) e = hipEventSynchronize(e1);
-                float ms = 0.f;
-                if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-                if (e != hipSuccess) {
-                    rc = hip_err(c, e, "autotune timing");
-                    break;
-                }
-                const double per = (double)ms / reps;
-                if (per < bms) {
-                    bms = per;
-                    bt = t;
-                }
-            }
+        nbody_tile t = cand[ci];
+        t.split = choose_split(p, n_i, n_j, t);
+        double per = 0.0;
+        rc = timed([&] {
+            return run_force(c, st, p, G, eps, n_i, ip, nullptr, nullptr, 0, n_j, (const float4*)c->jpack.p, o, &t);
+        }, &per);
+        if (!rc && per < bms) {
+            bms = per;
+            bt = t;
+        }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
-    c->tune.store(p, n_i, n_j, bt, bms);
+    c->tune.store(p, n_i, n_j, bt, bms, sym_ms);
     if (!c->tune.save()) return set_err(c, NBODY_ERR_ARG, "cannot write tune cache %s", c->tune.path().c_str());
     if (best) *best = bt;
     if (best_ms) *best_ms = bms;

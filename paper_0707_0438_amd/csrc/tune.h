@@ -29,6 +29,7 @@ class TuneCache {
         int prec, bi, bj;
         nbody_tile t;
         double ms;
+        double sym_ms;   // the pair-symmetric evaluation of that set (0: not timed)
     };
 
     void set_path(const char* p) { path_ = p ? p : ""; }
@@ -38,6 +39,14 @@ class TuneCache {
         if (colon != std::string::npos) arch_.resize(colon);
     }
     const std::string& path() const { return path_; }
+
+    // Whether the tuned shape was faster than the pair-symmetric evaluation.
+    bool beats_symmetric(int prec, int64_t n) const {
+        const int b = log2_bucket(n);
+        for (const Entry& e : entries_)
+            if (e.prec == prec && e.bi == b && e.bj == b) return e.sym_ms > 0.0 && e.ms < e.sym_ms;
+        return false;
+    }
 
     bool lookup(int prec, int64_t ni, int64_t nj, nbody_tile* out) const {
         const int bi = log2_bucket(ni), bj = log2_bucket(nj);
@@ -49,20 +58,22 @@ class TuneCache {
         return false;
     }
 
-    void store(int prec, int64_t ni, int64_t nj, const nbody_tile& t, double ms) {
+    void store(int prec, int64_t ni, int64_t nj, const nbody_tile& t, double ms, double sym_ms = 0.0) {
         const int bi = log2_bucket(ni), bj = log2_bucket(nj);
         for (Entry& e : entries_)
             if (e.prec == prec && e.bi == bi && e.bj == bj) {
                 e.t = t;
                 e.ms = ms;
+                e.sym_ms = sym_ms;
                 return;
             }
-        entries_.push_back(Entry{prec, bi, bj, t, ms});
+        entries_.push_back(Entry{prec, bi, bj, t, ms, sym_ms});
     }
 
     // Lines look like
     // {"arch": "gfx950", "prec": 1, "ni_log2": 20, "nj_log2": 20, "tile_j": 128, "ipt": 2, "wg": 256,
-    //  "split": 1, "jsrc": 0, "unroll": 0, "waves": 0, "ms": 812.5}   (one line)
+    //  "split": 1, "jsrc": 0, "unroll": 0, "waves": 0, "ms": 812.5, "sym_ms": 0.0}   (one line; without
+    //  sym_ms: the pair-symmetric evaluation was not timed)
     void load() {
         if (path_.empty()) return;
         FILE* f = fopen(path_.c_str(), "r");
@@ -74,10 +85,10 @@ class TuneCache {
             const int got = sscanf(line,
                                    " {\"arch\": \"%63[^\"]\", \"prec\": %d, \"ni_log2\": %d, \"nj_log2\": %d, "
                                    "\"tile_j\": %d, \"ipt\": %d, \"wg\": %d, \"split\": %d, \"jsrc\": %d, "
-                                   "\"unroll\": %d, \"waves\": %d, \"ms\": %lf",
+                                   "\"unroll\": %d, \"waves\": %d, \"ms\": %lf, \"sym_ms\": %lf",
                                    arch, &e.prec, &e.bi, &e.bj, &e.t.tile_j, &e.t.ipt, &e.t.wg, &e.t.split, &e.t.jsrc,
-                                   &e.t.unroll, &e.t.waves, &e.ms);
-            if (got == 12 && arch_ == arch) store_entry(e);
+                                   &e.t.unroll, &e.t.waves, &e.ms, &e.sym_ms);
+            if (got >= 12 && arch_ == arch) store_entry(e);
         }
         fclose(f);
     }
@@ -91,9 +102,9 @@ class TuneCache {
             fprintf(f,
                     "{\"arch\": \"%s\", \"prec\": %d, \"ni_log2\": %d, \"nj_log2\": %d, \"tile_j\": %d, "
                     "\"ipt\": %d, \"wg\": %d, \"split\": %d, \"jsrc\": %d, \"unroll\": %d, \"waves\": %d, "
-                    "\"ms\": %.6f}\n",
+                    "\"ms\": %.6f, \"sym_ms\": %.6f}\n",
                     arch_.c_str(), e.prec, e.bi, e.bj, e.t.tile_j, e.t.ipt, e.t.wg, e.t.split, e.t.jsrc, e.t.unroll,
-                    e.t.waves, e.ms);
+                    e.t.waves, e.ms, e.sym_ms);
         fclose(f);
         return rename(tmp.c_str(), path_.c_str()) == 0;
     }
