@@ -217,7 +217,7 @@ int nbody_force(nbody_ctx *ctx, hipStream_t stream, nbody_prec prec, double G, d
 
 /* nbody_force without any device allocation, for callers that cannot
  * allocate: code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc.  Same arguments, outputs and errors as nbody_force.
+ * that forbid hipMalloc.  Arguments, outputs and errors as nbody_force's.
  * Its packed particle records and split partial sums live in one 64 MiB
  * array of device memory per GPU that the library holds from its first
  * context on that device until the process ends; the call allocates and
@@ -228,7 +228,9 @@ int nbody_force(nbody_ctx *ctx, hipStream_t stream, nbody_prec prec, double G, d
  * nbody_last_error.  When the split partial sums (56 bytes per i and
  * j-range) of the launch shape nbody_force would use do not fit in the
  * rest, fewer j-ranges are used; the results then differ from
- * nbody_force's in rounding only.  Every call on one GPU uses that GPU's
+ * nbody_force's in rounding only.  So do those of a set that nbody_force
+ * evaluates pair by pair: the general kernel evaluates it here, in the time
+ * that takes.  Every call on one GPU uses that GPU's
  * array, across all contexts: two calls that overlap in time on one GPU
  * (different streams, threads or contexts) race and give wrong results.
  * Nothing in the array needs to start at zero.  NBODY_DEBUG_SELF_CHECK and
