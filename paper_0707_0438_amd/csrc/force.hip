@@ -324,17 +324,24 @@ hipError_t launch_batch_plan(const PlanArgs& p, hipStream_t st) {
 constexpr bool two_waves(int64_t groups, int wg) { return groups * wg > 1024 * 64; }
 template <int TJ>
 static bool use_prio(int64_t groups, int wg, const ForceArgs& a) {
-    return TJ >= 64 && (two_waves(groups, wg) || a.jchunk > TJ);
+    return two_waves(groups, wg) || a.jchunk > TJ;
+}
+
+template <int PREC, int IPT, int TJ, int WG, bool EPS0, int UNR, int WPE, bool PRIO>
+static void launch_prio(int nb, int S, const ForceArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL((force_kernel<PREC, IPT, TJ, WG, EPS0, UNR, WPE, PRIO>), dim3(nb, S), dim3(WG), 0, st, a);
 }
 
 template <int PREC, int IPT, int TJ, int WG, bool EPS0, int UNR, int WPE>
 static hipError_t launch_one(int nb, int S, const ForceArgs& a, hipStream_t st) {
     if constexpr (TJ < 64) {
-        hipLaunchKernelGGL((force_kernel<PREC, IPT, TJ, WG, EPS0, UNR, WPE, false>), dim3(nb, S), dim3(WG), 0, st, a);
-    } else if (IPT > 1 || use_prio<TJ>((int64_t)nb * S, WG, a)) {
-        hipLaunchKernelGGL((force_kernel<PREC, IPT, TJ, WG, EPS0, UNR, WPE, true>), dim3(nb, S), dim3(WG), 0, st, a);
+        launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, false>(nb, S, a, st);
+    } else if constexpr (IPT > 1) {
+        launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, true>(nb, S, a, st);
+    } else if (use_prio<TJ>((int64_t)nb * S, WG, a)) {
+        launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, true>(nb, S, a, st);
     } else {
-        hipLaunchKernelGGL((force_kernel<PREC, IPT, TJ, WG, EPS0, UNR, WPE, IPT != 1>), dim3(nb, S), dim3(WG), 0, st, a);
+        launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, false>(nb, S, a, st);
     }
     return hipGetLastError();
 }
@@ -345,13 +352,20 @@ static hipError_t launch_one_js(int nb, int S, const ForceArgs& a, hipStream_t s
     return hipGetLastError();
 }
 
+template <int PREC, int KIND, int IPT, int TJ, int WG, bool EPS0, int UNR, bool PRIO>
+static void launch_kind_prio(int nb, int S, const ForceArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL((force_kernel_kind<PREC, KIND, IPT, TJ, WG, EPS0, UNR, PRIO>), dim3(nb, S), dim3(WG), 0, st, a);
+}
+
 template <int PREC, int KIND, int IPT, int TJ, int WG, bool EPS0, int UNR>
 static hipError_t launch_kind(int nb, int S, const ForceArgs& a, hipStream_t st) {
-    if (IPT > 1 || use_prio<TJ>((int64_t)nb * S, WG, a))
-        hipLaunchKernelGGL((force_kernel_kind<PREC, KIND, IPT, TJ, WG, EPS0, UNR, true>), dim3(nb, S), dim3(WG), 0, st, a);
-    else
-        hipLaunchKernelGGL((force_kernel_kind<PREC, KIND, IPT, TJ, WG, EPS0, UNR, IPT != 1>), dim3(nb, S), dim3(WG), 0,
-                           st, a);
+    if constexpr (IPT > 1) {
+        launch_kind_prio<PREC, KIND, IPT, TJ, WG, EPS0, UNR, true>(nb, S, a, st);
+    } else if (use_prio<TJ>((int64_t)nb * S, WG, a)) {
+        launch_kind_prio<PREC, KIND, IPT, TJ, WG, EPS0, UNR, true>(nb, S, a, st);
+    } else {
+        launch_kind_prio<PREC, KIND, IPT, TJ, WG, EPS0, UNR, false>(nb, S, a, st);
+    }
     return hipGetLastError();
 }
 

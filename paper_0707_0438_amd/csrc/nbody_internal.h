@@ -479,24 +479,18 @@ hipError_t launch_predict_all(int n, const double* const* state /*x y z vx vy vz
 // j-parallel loop of small blocks gain nothing and keep the plain v_rsq.
 template <int N>
 __device__ __forceinline__ void rsq_group(float (&r)[N], const float (&s)[N]) {
-    static_assert(N == 1 || N == 2 || N == 4 || N == 8, "group size");
+    static_assert(N == 1 || N == 2 || N == 4, "group size");
     if constexpr (N == 1)
         asm("s_setprio 3\n\tv_rsq_f32 %0, %1\n\ts_setprio 0" : "=v"(r[0]) : "v"(s[0]));
     else if constexpr (N == 2)
         asm("s_setprio 3\n\tv_rsq_f32 %0, %2\n\tv_rsq_f32 %1, %3\n\ts_setprio 0"
             : "=&v"(r[0]), "=v"(r[1])
             : "v"(s[0]), "v"(s[1]));
-    else {
+    else
         asm("s_setprio 3\n\tv_rsq_f32 %0, %4\n\tv_rsq_f32 %1, %5\n\tv_rsq_f32 %2, %6\n\t"
             "v_rsq_f32 %3, %7\n\ts_setprio 0"
             : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=v"(r[3])
             : "v"(s[0]), "v"(s[1]), "v"(s[2]), "v"(s[3]));
-        if constexpr (N == 8)
-            asm("s_setprio 3\n\tv_rsq_f32 %0, %4\n\tv_rsq_f32 %1, %5\n\tv_rsq_f32 %2, %6\n\t"
-                "v_rsq_f32 %3, %7\n\ts_setprio 0"
-                : "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=v"(r[7])
-                : "v"(s[4]), "v"(s[5]), "v"(s[6]), "v"(s[7]));
-    }
 }
 
 // Hermite predictor (float64), Horner form of
