@@ -53,10 +53,9 @@ void force_kernel(ForceArgs a) {
     constexpr bool LOW = unr_low(UNR);
     __shared__ float4 sh[LOW ? 1 : 2][TJ * Rec<PREC>::R];
     __shared__ float losh[LOW && PREC == 1 ? 7 * IPT * WG : 1];
-    if (a.only && *a.only != a.epoch) return;
     const int jb = blockIdx.y * a.jchunk;
     const int je = min(a.nj, jb + a.jchunk);
-    force_block<PREC, IPT, TJ, WG, EPS0, false, unr_depth(UNR), unr_pipe(UNR), 0, LOW, PRIO>(
+    force_block<PREC, IPT, TJ, WG, EPS0, false, unr_depth(UNR), unr_pipe(UNR), 0, LOW, PRIO, true>(
         a, sh, blockIdx.x * (WG * IPT), a.ni, jb, je, a.eps2, blockIdx.y, losh);
 }
 
@@ -64,10 +63,9 @@ void force_kernel(ForceArgs a) {
 template <int PREC, int KIND, int IPT, int TJ, int WG, bool EPS0, int UNR, bool PRIO>
 __global__ __launch_bounds__(WG) void force_kernel_kind(ForceArgs a) {
     __shared__ float4 sh[2][TJ * Rec<PREC>::R];
-    if (a.only && *a.only != a.epoch) return;
     const int jb = blockIdx.y * a.jchunk;
     const int je = min(a.nj, jb + a.jchunk);
-    force_block<PREC, IPT, TJ, WG, EPS0, false, unr_depth(UNR), unr_pipe(UNR), KIND, false, PRIO>(
+    force_block<PREC, IPT, TJ, WG, EPS0, false, unr_depth(UNR), unr_pipe(UNR), KIND, false, PRIO, true>(
         a, sh, blockIdx.x * (WG * IPT), a.ni, jb, je, a.eps2, blockIdx.y);
 }
 
@@ -103,8 +101,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE > 0 ? WP
 void force_kernel_js(ForceArgs a) {
     const int jb = blockIdx.y * a.jchunk;
     const int je = min(a.nj, jb + a.jchunk);
-    force_block<PREC, IPT, TJ, WG, EPS0, true, UNR>(a, nullptr, blockIdx.x * (WG * IPT), a.ni, jb, je, a.eps2,
-                                                     blockIdx.y);
+    force_block<PREC, IPT, TJ, WG, EPS0, true, UNR, false, 0, false, true, true>(
+        a, nullptr, blockIdx.x * (WG * IPT), a.ni, jb, je, a.eps2, blockIdx.y);
 }
 
 // Many independent clusters in one persistent launch.  Work items
@@ -140,8 +138,9 @@ __device__ __forceinline__ double reduce_finish(const ReduceArgs& a, int q, doub
     return q < 6 ? a.G * s : -a.G * s;
 }
 
+template <bool GUARD>
 __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
-    if (a.only && *a.only != a.epoch) return;
+    if (GUARD && *a.only != a.epoch) return;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= 7 * (int64_t)a.ni) return;
     const int q = (int)(t / a.ni);
@@ -156,8 +155,9 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
     a.out[q][i] = reduce_finish(a, q, s);
 }
 
+template <bool GUARD>
 __global__ __launch_bounds__(256) void reduce_wave_kernel(ReduceArgs a) {
-    if (a.only && *a.only != a.epoch) return;
+    if (GUARD && *a.only != a.epoch) return;
     const int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int lane = threadIdx.x & 63;
     if (w >= 7 * (int64_t)a.ni) return;   // whole waves leave together
@@ -179,9 +179,10 @@ __global__ __launch_bounds__(256) void reduce_wave_kernel(ReduceArgs a) {
 // 512 contiguous bytes (reduce_wave_kernel's lanes read 64 rows); then the
 // eight sums in order.  Evaluations of N = 5000 51.5 to 39 us, 8192 82 to 64;
 // fewer i leave too few work-groups (128 i, 2048 ranges: 58 to 68 us).
+template <bool GUARD>
 __global__ __launch_bounds__(512) void reduce_rows_kernel(ReduceArgs a) {
     __shared__ double sum[8][64];
-    if (a.only && *a.only != a.epoch) return;
+    if (GUARD && *a.only != a.epoch) return;
     const int q = blockIdx.y;
     if (!a.out[q]) return;   // a row the evaluation does not produce
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -242,16 +243,24 @@ hipError_t launch_nn_reduce(int ni, int S, const float2* nnpart, int32_t* nn, do
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st) {
-    if (a.ni <= 0) return hipSuccess;
+template <bool GUARD>
+static void launch_reduce_guard(const ReduceArgs& a, hipStream_t st) {
     const int64_t n = 7 * (int64_t)a.ni;
     if (a.S >= 32 && a.ni >= 512) {
-        hipLaunchKernelGGL(reduce_rows_kernel, dim3((a.ni + 63) / 64, 7), dim3(512), 0, st, a);
+        hipLaunchKernelGGL(reduce_rows_kernel<GUARD>, dim3((a.ni + 63) / 64, 7), dim3(512), 0, st, a);
     } else if (a.S >= 32) {
-        hipLaunchKernelGGL(reduce_wave_kernel, dim3((unsigned)((n * 64 + 255) / 256)), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(reduce_wave_kernel<GUARD>, dim3((unsigned)((n * 64 + 255) / 256)), dim3(256), 0, st, a);
     } else {
-        hipLaunchKernelGGL(reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(reduce_kernel<GUARD>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
     }
+}
+
+hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st) {
+    if (a.ni <= 0) return hipSuccess;
+    if (a.only)
+        launch_reduce_guard<true>(a, st);
+    else
+        launch_reduce_guard<false>(a, st);
     return hipGetLastError();
 }
 

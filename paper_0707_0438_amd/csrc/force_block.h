@@ -62,9 +62,9 @@ __device__ __forceinline__ void two_sum_fold(float& hi, float& lo, float p) {
 // touches its own words once per tile) and the j tiles are single-buffered
 // (sh[0] only), so no staging registers stay live through the tile loop.
 // PRIO: v_rsq in groups at raised priority (rsq_group), for launches with
-// more than one wave per SIMD.
+// more than one wave per SIMD.  GUARD: honours a.only.
 template <int PREC, int IPT, int TJ, int WG, bool EPS0, bool JS = false, int UNR = 4, bool PIPE = false,
-          int KIND = 0, bool LOW = false, bool PRIO = true>
+          int KIND = 0, bool LOW = false, bool PRIO = true, bool GUARD = false>
 __device__ __forceinline__ void force_block(const ForceArgs& a, float4 (*sh)[TJ * Rec<PREC>::R], int ibase,
                                             int iend, int jb, int je, float eps2, int split,
                                             float* __restrict__ losh = nullptr) {
@@ -246,6 +246,9 @@ __device__ __forceinline__ void force_block(const ForceArgs& a, float4 (*sh)[TJ 
 
     const std::integral_constant<bool, false> plain{};
     const std::integral_constant<bool, true> masked{};
+    // behind the i loads: in front of them every launch, guarded or not, waits
+    // for one more scalar load first (force-only, 3226 bodies: 13.8 to 14.1 us)
+    if (GUARD && a.only && *a.only != a.epoch) return;
     if (JS) {
         // j records read by wave-uniform loads (scalar data cache); chunks of
         // TJ j between compensated folds; no LDS, no barrier

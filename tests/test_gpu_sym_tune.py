@@ -58,3 +58,27 @@ def test_tuned_shape_and_symmetric_evaluation(tmp_path):
         assert _equal(c.force(x, v, x, v, m, EPS, i_self=own), sym) == (e["sym_ms"] <= e["ms"])
         c.autotune(x.clone(), v, x, v, m, EPS, prec="ds", reps=1)
         assert json.loads(cache.read_text())["sym_ms"] == 0
+
+
+@pytest.mark.parametrize("jsrc,tile_j,wg", [(0, 256, 256), (1, 128, 256)])
+def test_tuned_shape_behind_the_symmetric_evaluation(jsrc, tile_j, wg, tmp_path):
+    """The kernel launched behind, in a tuned shape with one j-range (so that
+    it would write the outputs itself), leaves them as they are; where i_self
+    is not the identity it does the work."""
+    import torch
+    import paper_0707_0438_amd as nb
+    s = _set()
+    x, v, m, own = s
+    shape = dict(tile_j=tile_j, ipt=1, wg=wg, split=1, jsrc=jsrc, unroll=0, waves=0)
+    sym, shaped = _force(s), _force(s, tile=shape)
+    assert not _equal(sym, shaped)
+    cache = tmp_path / "tune.jsonl"
+    cache.write_text(json.dumps(dict(arch="gfx950", prec=1, ni_log2=14, nj_log2=14, **shape, ms=1.0, sym_ms=0.5)) + "\n")
+    assert _equal(_force(s, str(cache)), sym)
+    other = own.clone()
+    other[0] = -1
+    with nb.Context(0, tune_cache=str(cache)) as c:
+        got = c.force(x, v, x, v, m, EPS, i_self=other)
+        c.set_tile("ds", **shape)
+        assert _equal(got, c.force(x, v, x, v, m, EPS, i_self=other))
+        torch.cuda.synchronize()
