@@ -95,13 +95,16 @@ __global__ __launch_bounds__(WG) void force_kernel_plan(ForceArgs a) {
 
 // Same work with the j records read through the scalar data cache instead of
 // LDS (every lane of a wave needs the same j record, so one wave-uniform load
-// serves the wave).  TJ only sets the compensated-fold interval.
+// serves the wave).  TJ only sets the compensated-fold interval.  DS with one
+// i per lane keeps the plain v_rsq: a group of one gains nothing there and its
+// inline assembly keeps the loop from unrolling (65536 bodies 6.64 against
+// 6.33 ms); the others gain 6 to 26% from the groups all the same.
 template <int PREC, int IPT, int TJ, int WG, bool EPS0, int UNR, int WPE>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE > 0 ? WPE : 1)))
 void force_kernel_js(ForceArgs a) {
     const int jb = blockIdx.y * a.jchunk;
     const int je = min(a.nj, jb + a.jchunk);
-    force_block<PREC, IPT, TJ, WG, EPS0, true, UNR, false, 0, false, true, true>(
+    force_block<PREC, IPT, TJ, WG, EPS0, true, UNR, false, 0, false, PREC == 0 || (IPT > 1), true>(
         a, nullptr, blockIdx.x * (WG * IPT), a.ni, jb, je, a.eps2, blockIdx.y);
 }
 
