@@ -327,16 +327,22 @@ hipError_t launch_batch_plan(const PlanArgs& p, hipStream_t st) {
 
 // Whether a launch puts more than one wave on each of the 1024 SIMDs.  Below
 // that a wave issues alone: it never loses the two-wave issue that the
-// raised priority of rsq_group keeps, only pays for it (force-only at N =
-// 2000, 992 waves of one tile each, 2% slower; 64 float32 clusters of at
-// most 1024 bodies, 400 waves, 6%).  Direct launches whose ranges hold more
-// than one tile gain all the same, from the four records in flight (N = 2100,
-// 578 waves: 28.7 to 26.9 us); N = 3000, 2256 waves: 35.8 to 30.4 us.  The
-// short tiles serve one-tile ranges only.
+// raised priority of rsq_group keeps, only pays for it (64 float32 clusters of
+// at most 1024 bodies, 400 waves, 6%).
 constexpr bool two_waves(int64_t groups, int wg) { return groups * wg > 1024 * 64; }
-template <int TJ>
+
+// Direct launches of one i per lane whose v_rsq stand in groups.  Ranges of
+// more than one tile gain below two waves too, from the four records in
+// flight, once some CU has two work-groups (DS, kernel time, plain to grouped:
+// 2100 bodies, 289 work-groups, 23.6 to 21.8 us, force-only 17.9 to 17.5; 1943
+// bodies, 256 work-groups, force-only 16.2 to 17.0, with neighbours 22.7 to
+// 23.2).  The float32 full evaluation gains from more than two waves per SIMD
+// only (3226 bodies, 1.3 waves, 21.4 to 22.5 us; 3820, 1.8, 21.4 to 22.1;
+// 4600, 2.5, 30.7 to 28.4).
+template <int PREC, int KIND, int TJ>
 static bool use_prio(int64_t groups, int wg, const ForceArgs& a) {
-    return two_waves(groups, wg) || a.jchunk > TJ;
+    if (PREC == 0 && KIND == 0) return groups * wg > 2 * 1024 * 64;
+    return two_waves(groups, wg) || (a.jchunk > TJ && groups > 256);
 }
 
 template <int PREC, int IPT, int TJ, int WG, bool EPS0, int UNR, int WPE, bool PRIO>
@@ -346,11 +352,11 @@ static void launch_prio(int nb, int S, const ForceArgs& a, hipStream_t st) {
 
 template <int PREC, int IPT, int TJ, int WG, bool EPS0, int UNR, int WPE>
 static hipError_t launch_one(int nb, int S, const ForceArgs& a, hipStream_t st) {
-    if constexpr (TJ < 64) {
+    if constexpr (TJ < 64) {   // short tiles serve one-tile ranges only
         launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, false>(nb, S, a, st);
     } else if constexpr (IPT > 1) {
         launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, true>(nb, S, a, st);
-    } else if (use_prio<TJ>((int64_t)nb * S, WG, a)) {
+    } else if (use_prio<PREC, 0, TJ>((int64_t)nb * S, WG, a)) {
         launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, true>(nb, S, a, st);
     } else {
         launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, false>(nb, S, a, st);
@@ -373,7 +379,7 @@ template <int PREC, int KIND, int IPT, int TJ, int WG, bool EPS0, int UNR>
 static hipError_t launch_kind(int nb, int S, const ForceArgs& a, hipStream_t st) {
     if constexpr (IPT > 1) {
         launch_kind_prio<PREC, KIND, IPT, TJ, WG, EPS0, UNR, true>(nb, S, a, st);
-    } else if (use_prio<TJ>((int64_t)nb * S, WG, a)) {
+    } else if (use_prio<PREC, KIND, TJ>((int64_t)nb * S, WG, a)) {
         launch_kind_prio<PREC, KIND, IPT, TJ, WG, EPS0, UNR, true>(nb, S, a, st);
     } else {
         launch_kind_prio<PREC, KIND, IPT, TJ, WG, EPS0, UNR, false>(nb, S, a, st);
