@@ -47,8 +47,16 @@ constexpr int unr_depth(int u) { return u % 100; }
 constexpr bool unr_pipe(int u) { return (u / 100) % 2 == 1; }
 constexpr bool unr_low(int u) { return u >= 200; }
 
+// Waves per SIMD asked of the default small-size shapes.  Float32, grouped
+// v_rsq: 67 registers by themselves, seven waves, and a launch that fills
+// eight waves exactly has a second round (4096 i against 524288 j: 1.27 ms
+// with the plain form, 1.33); 63 registers when asked, at no instruction more.
+constexpr int small_waves(int prec, int ipt, int tj, bool prio) {
+    return prec == 0 && ipt == 1 && tj == 64 && prio ? 8 : 1;
+}
+
 template <int PREC, int IPT, int TJ, int WG, bool EPS0, int UNR, int WPE, bool PRIO>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE > 0 ? WPE : 1)))
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE > 0 ? WPE : small_waves(PREC, IPT, TJ, PRIO))))
 void force_kernel(ForceArgs a) {
     constexpr bool LOW = unr_low(UNR);
     __shared__ float4 sh[LOW ? 1 : 2][TJ * Rec<PREC>::R];
