@@ -59,20 +59,28 @@ constexpr int64_t kLongTiles = 64;
 // The long-evaluation split keeps its partial sums (8 rows of 8 bytes per
 // i and range at most) within this many bytes.
 constexpr int64_t kLongPartBytes = (int64_t)1 << 31;
+// Ranges of five tiles that hold nj records (the last may be shorter).
+inline int64_t fine_ranges(int64_t nj, const nbody_tile& t) { return (nj + 5 * t.tile_j - 1) / (5 * t.tile_j); }
 inline int choose_split(int prec, int64_t ni, int64_t nj, const nbody_tile& t, int kind = 0) {
     int nb, S, jc;
     split_plan(ni, nj, t.wg * t.ipt, t.tile_j, 0, &nb, &S, &jc);
-    // 64-record tiles, DS: twice the work-groups of split_plan as long as a
-    // range keeps five tiles: more than the chip holds at once, so the CUs
-    // fill up evenly.  One round depends on how the dispatcher happens to
-    // spread it (N = 16384, 2048 work-groups: 201 or 231 us by which kernel
-    // ran before; 4096: 204).  N = 23000 435 to 390 us, 12000 i against 65536
-    // j 646 to 587; N = 8192, two tiles a range, would lose 4%.  The other
-    // kinds' shorter loops gain from 24 tiles a range on only (force-only,
-    // N = 20001, 23 tiles: 184 to 196 us).  Float32 keeps its ranges: each is
-    // one float32 sum.
+    // 64-record tiles, DS: twice the work-groups of split_plan, in ranges of
+    // five tiles or more: more than the chip holds at once (2560: ten a CU), so
+    // the CUs fill up evenly.  One round depends on how the dispatcher happens
+    // to spread it (N = 16384, 2048 work-groups: 201 or 231 us by which kernel
+    // ran before; 4096: 204).  Coarse to fine, whole calls: N = 12000 122 to
+    // 114 us, 18000 261 to 247, 22000 390 to 354, 30000 698 to 637, 1500 i
+    // against 262144 j 355 to 300; N = 20001 loses (288 to 297), and N = 8192
+    // would, with two tiles a range (4%).  Five tiles to the record: rounded
+    // down to fewer ranges they are six, and 2560 to 3000 work-groups, a
+    // second round for a few of them (256 i against 524288 j: 137 us coarse,
+    // 141 in six tiles, 138 in five; N = 12000 127 in six).  The other kinds'
+    // shorter loops gain from 24 tiles a (coarse) range on only: neighbours at
+    // N = 20001, 22 tiles, 342 to 353 us, 22000, 29 tiles, 467 to 421, 40000
+    // 1483 to 1268; force-only 181 to 195, 244 to 233, 756 to 677.  Float32
+    // keeps its ranges: each is one float32 sum.
     if (prec == 1 && t.tile_j == 64 && nb > 0 && (kind == 0 || jc >= 24 * t.tile_j))
-        S = (int)std::max<int64_t>(S, std::min<int64_t>((4096 + nb - 1) / nb, nj / (5 * t.tile_j)));
+        S = (int)std::max<int64_t>(S, std::min((4096 + nb - 1) / (int64_t)nb, fine_ranges(nj, t)));
     const int64_t per = (int64_t)t.wg * t.ipt;
     const int64_t nbl = (ni + per - 1) / per;
     int64_t Sl = nbl > 0 ? (kLongWG + nbl - 1) / nbl : 1;
@@ -124,7 +132,7 @@ inline nbody_tile default_tile_kind(int kind, int prec, int64_t ni, int64_t nj) 
 inline int64_t split_bound(int prec, int64_t ni, int64_t nj, const nbody_tile& t) {
     const int64_t per = (int64_t)t.wg * t.ipt, nb = std::max<int64_t>(1, (ni + per - 1) / per);
     int64_t S = nb < 1024 ? std::min((2048 + nb - 1) / nb, nj / t.tile_j) : 1;
-    if (prec == 1 && t.tile_j == 64) S = std::max(S, std::min((4096 + nb - 1) / nb, nj / (5 * t.tile_j)));
+    if (prec == 1 && t.tile_j == 64) S = std::max(S, std::min((4096 + nb - 1) / nb, fine_ranges(nj, t)));
     const int64_t Sl = std::min((kLongWG + nb - 1) / nb, nj / (kLongTiles * t.tile_j));
     return std::max(S, std::min(Sl, kLongPartBytes / (64 * std::max<int64_t>(ni, 1))));
 }
