@@ -47,16 +47,8 @@ constexpr int unr_depth(int u) { return u % 100; }
 constexpr bool unr_pipe(int u) { return (u / 100) % 2 == 1; }
 constexpr bool unr_low(int u) { return u >= 200; }
 
-// Waves per SIMD asked of the default small-size shapes.  Float32, grouped
-// v_rsq: 67 registers by themselves, seven waves, and a launch that fills
-// eight waves exactly has a second round (4096 i against 524288 j: 1.27 ms
-// with the plain form, 1.33); 63 registers when asked, at no instruction more.
-constexpr int small_waves(int prec, int ipt, int tj, bool prio) {
-    return prec == 0 && ipt == 1 && tj == 64 && prio ? 8 : 1;
-}
-
 template <int PREC, int IPT, int TJ, int WG, bool EPS0, int UNR, int WPE, bool PRIO>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE > 0 ? WPE : small_waves(PREC, IPT, TJ, PRIO))))
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(WPE > 0 ? WPE : 1)))
 void force_kernel(ForceArgs a) {
     constexpr bool LOW = unr_low(UNR);
     __shared__ float4 sh[LOW ? 1 : 2][TJ * Rec<PREC>::R];
@@ -365,7 +357,17 @@ static hipError_t launch_one(int nb, int S, const ForceArgs& a, hipStream_t st) 
     } else if constexpr (IPT > 1) {
         launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, true>(nb, S, a, st);
     } else if (use_prio<PREC, 0, TJ>((int64_t)nb * S, WG, a)) {
-        launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, true>(nb, S, a, st);
+        // Float32, 64-record tiles: 67 registers by itself, seven waves per
+        // SIMD, and a launch that fills eight has a second round (4096 i
+        // against 524288 j 1.31 ms before the groups, 1.33 with them; 1000
+        // against 2^21 1.38).  It takes 63 when asked for eight: 1.20 and 1.25.
+        // A launch of up to seven waves lies evenly on the CUs only if they
+        // hold no more (2500 against 700000: 1.09 ms, 1.16 when asked).
+        constexpr int kWaves = PREC == 0 && TJ == 64 && WPE == 0 ? 8 : WPE;
+        if ((int64_t)nb * S * WG > 7 * 1024 * 64)
+            launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, kWaves, true>(nb, S, a, st);
+        else
+            launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, true>(nb, S, a, st);
     } else {
         launch_prio<PREC, IPT, TJ, WG, EPS0, UNR, WPE, false>(nb, S, a, st);
     }
