@@ -69,23 +69,33 @@ def profile_keys(path):
     return kv
 
 
-def traffic_per_launch(prec: str):
-    """HBM bytes per launch of the pairwise kernel from the committed rocprofv3
-    counter summary, or None when it is missing or the kernel source or the
-    launch-shape rules changed since the counters were taken."""
-    kv = profile_keys(TRAFFIC_FILE) if prec == "ds" else None
+def pair_symmetric(prec: str, n: int) -> bool:
+    """Whether the library evaluates a set of n pair by pair in its default
+    launch shapes (see nbody_force); the counter summaries of double-single
+    are of that evaluation."""
+    pinned = os.environ.get("NBODY_FORCE_TILE") or os.environ.get("NBODY_TUNE_CACHE")
+    return prec == "ds" and 24576 <= n <= 1 << 24 and not pinned
+
+
+def traffic_per_launch(prec: str, n: int):
+    """HBM bytes per launch of the pairwise kernel at 2^20 particles from the
+    committed rocprofv3 counter summary, or None when it is missing, of other
+    sizes or another kernel, or the kernel source or the launch-shape rules
+    changed since the counters were taken."""
+    kv = profile_keys(TRAFFIC_FILE) if n == 1 << 20 and pair_symmetric(prec, n) else None
     try:
         return float(kv["traffic_bytes_per_launch"]) if kv else None
     except (KeyError, ValueError):
         return None
 
 
-def executed_flops(prec: str, gint_s: float):
+def executed_flops(prec: str, n: int, gint_s: float):
     """Executed FP32 flop rate of the pairwise kernel: the flop per interaction
     the VALU counters measured (ADD + MUL + TRANS + 2 FMA instructions x 64
     lanes, per interaction; committed summary, used only while the kernel
-    sources match) times the measured interaction rate.  None otherwise."""
-    kv = profile_keys(VALU_FILE)
+    sources match and for the kernel it is of) times the measured interaction
+    rate.  None otherwise."""
+    kv = profile_keys(VALU_FILE) if prec != "ds" or pair_symmetric(prec, n) else None
     key = ("ds" if prec == "ds" else "fp32") + "_executed_flop_per_interaction"
     try:
         f = float(kv[key]) if kv else None
@@ -641,7 +651,7 @@ def main():
     value = r["inter"] / r["wall"] / 1e9
     k_ms = r["kms"] / max(r["launches"], 1)
     achieved = FLOPS_PER_INTERACTION * float(n) * n / (k_ms * 1e-3) / 1e12
-    traffic = traffic_per_launch(args.prec)
+    traffic = traffic_per_launch(args.prec, n)
     line = {
         "metric": "Ginteractions/s (acc+jerk) at N=2^20, % FP32 peak; adjoint/forward time",
         "value": round(value, 3),
@@ -672,7 +682,8 @@ def main():
             "unit": "TFLOP/s",
             "frac": round(achieved / FP32_PEAK_TFLOPS, 4),
             "traffic": traffic,
-            "kernel": ("sym_kernel" if args.prec == "ds" else "force_kernel") + " (pairwise acc+jerk+pot)",
+            "flops_per_interaction": f"{FLOPS_PER_INTERACTION} (convention; see executed)",
+            "kernel": ("sym_kernel" if pair_symmetric(args.prec, n) else "force_kernel") + " (pairwise acc+jerk+pot)",
             "kernel_ms": round(k_ms, 3),
             "launches": r["launches"],
         },
@@ -687,7 +698,7 @@ def main():
             "kernel_ms": round(o["kms"] / max(o["launches"], 1), 3),
             "pct_fp32_peak": round(100.0 * FLOPS_PER_INTERACTION * ov * 1e9 / (FP32_PEAK_TFLOPS * 1e12), 2),
         }
-    line["executed"] = executed_flops(args.prec, float(n) * n / (k_ms * 1e-3) / 1e9)
+    line["executed"] = executed_flops(args.prec, n, float(n) * n / (k_ms * 1e-3) / 1e9)
     extras = [] if args.extras == "none" else args.extras.split(",")
     precs = (args.prec, other)
     pname = lambda q: "ds_comp" if q == "ds" else "fp32"
