@@ -202,7 +202,7 @@ int nbody_autotune(nbody_ctx *ctx, hipStream_t stream, nbody_prec prec, double G
  * that nbody_autotune found to be faster) is
  * evaluated pair by pair, each pair serving both of its particles: the same
  * float32 partial sums, added up in another order (differences of order
- * 1e-14), with at most 2 GiB of scratch; where that cannot be had, the
+ * 1e-14 in the norm, up to 1e-12 of a single value), with at most 2 GiB of scratch; where that cannot be had, the
  * general kernel runs, and does so for sets of that size or more until the
  * context's next nbody_reserve.  An i_self value outside [0, n_j) excludes
  * nothing.  With the environment variable NBODY_DEBUG_SELF_CHECK=1 set when

@@ -2018,10 +2018,11 @@ static nbody_tile batched_tile(nbody_ctx* c, int prec, int64_t n_total, int32_t 
         t = c->override_tile[prec];
     } else if (!c->tune.lookup(prec + 2, n_total, n_clusters, &t)) {
         // 256 lanes where that still gives every CU many work-groups, 128
-        // for fewer, which then end closer together (512 clusters of 64 to
-        // 8192 bodies, 6800 groups of 128: 2.74 to 2.65 ms DS, 2.46 to 2.21
-        // float32; 64 clusters, 850 groups: 0.76 against 0.77 and 0.68
-        // against 0.70)
+        // for few, which then end closer together (64 clusters of 64 to 1024
+        // bodies, 850 groups of 128: 0.76 against 0.77 ms DS, 0.68 against
+        // 0.70 float32; 512 of up to 8192, 6800 groups: 2.66 to 2.56 and 2.39
+        // to 2.13).  The line is on the safe side: 120 clusters of up to 8192
+        // bodies, 201012 in all, gain 9 and 12% too
         t.tile_j = 128;
         t.ipt = 1;
         t.wg = n_total >= 4096 * 128 ? 256 : 128;

@@ -183,7 +183,9 @@ struct SymShape {
 constexpr int64_t kSymBytes = (int64_t)1 << 31;
 constexpr int kSymGroup = 1024;      // i-particles a work-group holds at a time
 constexpr int kSymResident = 1024;   // work-groups on the chip at once: four per CU
-constexpr int64_t kSymMin = 24576;   // 20001 bodies: 344 us against the general kernel's 291; 26000: 488 against 526
+// 20001 bodies: 344 us against the general kernel's 291; 25001: 435 against
+// 446; force-only 26001: 283 against 311
+constexpr int64_t kSymMin = 24576;
 constexpr int64_t kSymMax = (int64_t)1 << 24;   // beyond, two rows pass kSymBytes (112 B a particle)
 // rows are padded to whole groups, so a shape depends on n by its groups only
 constexpr int64_t sym_stride(int64_t n) { return (n + kSymGroup - 1) / kSymGroup * kSymGroup; }
