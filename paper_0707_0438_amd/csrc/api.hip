@@ -652,7 +652,7 @@ static int need_device(nbody_ctx* c) {
 static size_t reserve_part_bytes(nbody_ctx* c, int64_t max_i, int64_t max_j) {
     const int64_t ni = std::max<int64_t>(max_i, 1), nj = std::max<int64_t>(max_j, 1);
     size_t part = 0;
-    for (int kind = 0; kind < 3; ++kind)
+    for (int kind = 0; kind < 2; ++kind)   // (the two kinds other than the full one have the same shapes)
         for (int prec = 0; prec < 2; ++prec) {
             const int64_t rows = part_rows_upto(
                 prec, ni, nj, [&](int64_t n, int64_t m) { return base_tile(c, kind, prec, n, m); });
